@@ -12,8 +12,8 @@
  * (sub-chunk) tiling of Sec. 4.3: an inter-chunk state pass, attention-like
  * intra-chunk blocks (bf16 matrix-core products between sub-chunks, with
  * normalisers at the sub-chunk boundaries; inside a sub-chunk, Eq. 4 itself
- * in fp32 on the vector ALUs: one exponential of the log-space difference
- * per pair and feature; with a scalar gate or none, every block is the
+ * in fp32 on the vector ALUs, each pair's decay the product of the steps'
+ * decays between its rows; with a scalar gate or none, every block is the
  * plain (Q K^T) (.) D, D_ij = exp(c_i - c_j), in fp32 on the matrix cores),
  * and the closed-form gate gradient of Sec. 4.3 in
  * the backward.
@@ -118,9 +118,9 @@ enum {
   GLA_FLAG_SCALAR_GATE = 1u << 1,
   /* Accepted for compatibility and without effect: every diagonal (within
    * one sub-chunk) block of the intra-chunk terms, forward and backward, is
-   * always evaluated in fp32 log space, one exponential exp(B_i - B_j) per
-   * pair and feature on the vector ALUs, as the paper prescribes for these
-   * blocks (Sec. 4.3).  Results are bit-identical with and without it. */
+   * always evaluated in fp32 on the vector ALUs without a division by a
+   * cumulative decay, as the paper prescribes for these blocks (Sec. 4.3).
+   * Results are bit-identical with and without it. */
   GLA_FLAG_FP32_DIAGONAL = 1u << 2,
   /* Bits 8..11 select a single stage of an entry point's launch sequence (0 =
    * the whole sequence), so that a profiler or benchmark can time each kernel

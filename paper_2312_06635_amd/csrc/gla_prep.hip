@@ -15,14 +15,19 @@
 //       (q_I (.) exp(B - z_I)) diag(exp(z_I - zend_J)) (k_J (.) exp(zend_J - B))^T
 //     with z_I the log decay at the start of block I and zend_J at the end of J.
 //   * I = J ("pink", inside a sub-chunk): Eq. 4 itself in fp32 on the vector
-//     ALUs, one exponential of the log-space difference B_ik - B_jk per pair
-//     and feature (Sec. 4.3: full precision, no division by a cumulative
-//     decay), the partial sums of a lane's features then reduced across the
-//     wave.  Any gate, however steep, is exact here: every exponent is <= 0.
+//     ALUs.  The decay exp(B_ik - B_jk) of a pair is the product of the step
+//     decays alpha between its rows, so one exponential per row and feature
+//     (alpha itself) serves all the pairs: inside each 8x8 triangle k_j's
+//     decayed value is carried from row to row (one multiply, one
+//     multiply-add per pair), and the 8x8 square below the triangles is a
+//     plain product of operands decayed to the boundary between them (one
+//     multiply-add per pair).  Full precision, no division by a cumulative
+//     decay, every factor <= 1: any gate, however steep, is exact here (a
+//     product of decays has a relative error of a few ulp, where an
+//     exponential of a difference has the rounding of the cumsums).  The
+//     partial sums of a lane's features are then reduced across the wave.
 // Sub-chunks shorter than 16 (c < 16) lie inside the diagonal blocks, whose
 // fp32 evaluation is the same for any such c.
-#include <type_traits>
-
 #include "gla_common.hpp"
 #include "gla_launch.hpp"
 
@@ -37,7 +42,7 @@ struct PrepArgs {
   float inv_tau;  // gate epilogue (0: la holds log alpha)
 };
 
-// Entry e of a 16x16 lower triangle (diagonal included), row-major.
+// Entry e of a lower triangle (diagonal included), row-major.
 __host__ __device__ constexpr int tri_row(int e) {
   int i = 0;
   while ((i + 1) * (i + 2) / 2 <= e) ++i;
@@ -45,34 +50,55 @@ __host__ __device__ constexpr int tri_row(int e) {
 }
 __host__ __device__ constexpr int tri_col(int e) { return e - tri_row(e) * (tri_row(e) + 1) / 2; }
 
-// Reduce-scatter of N (<= 32) partial sums per lane across the 64 lanes of a
-// wave: the two half-waves are added first, then on return lane l (and lane
-// l + 32) holds the wave's sum of x[l % N].
-template <int H, int N> __device__ __forceinline__ void rs_step(float (&x)[N], int l) {
-  const bool up = (l & H) != 0;
+// Partner's value inside a 16-lane row.
+template <int CTRL> __device__ __forceinline__ float dpp_row(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+
+// Reduce-scatter of 32 partial sums per lane across the 64 lanes of a wave: on
+// return lane l holds the wave's sum of x[l / 2].  A step with partner lanes
+// differing in bit b keeps, in each lane, the half of the values that the bit
+// selects; bits 5 and 4 are the half-wave and row swaps, whose two results
+// are the kept and the received halves at once.
+template <int CTRL, int H> __device__ __forceinline__ void rs_row(float (&x)[32], bool up) {
 #pragma unroll
   for (int e = 0; e < H; ++e) {
     const float send = up ? x[e] : x[e + H];
-    const float keep = up ? x[e + H] : x[e];
-    x[e] = keep + __shfl_xor(send, H);
+    x[e] = (up ? x[e + H] : x[e]) + dpp_row<CTRL>(send);
   }
 }
 __device__ __forceinline__ float reduce_scatter32(float (&x)[32]) {
   const int l = lane_id();
 #pragma unroll
-  for (int e = 0; e < 32; ++e) x[e] += __shfl_xor(x[e], 32);
-  rs_step<16>(x, l);
-  rs_step<8>(x, l);
-  rs_step<4>(x, l);
-  rs_step<2>(x, l);
-  rs_step<1>(x, l);
-  return x[0];
+  for (int e = 0; e < 16; ++e) {
+    // (the results are copied out first: a bit cast of a vector element reads element 0)
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x[e]),
+                                                    __builtin_bit_cast(uint32_t, x[e + 16]), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    x[e] = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    // (the results are copied out first: a bit cast of a vector element reads element 0)
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x[e]),
+                                                    __builtin_bit_cast(uint32_t, x[e + 8]), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    x[e] = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+  }
+  rs_row<0x128, 4>(x, (l & 8) != 0);  // row_ror:8, lane ^ 8
+  rs_row<0x141, 2>(x, (l & 4) != 0);  // row_half_mirror, lane ^ 7
+  rs_row<0x4E, 1>(x, (l & 2) != 0);   // quad_perm [2,3,0,1], lane ^ 2
+  return x[0] + dpp_row<0xB1>(x[0]);  // quad_perm [1,0,3,2], lane ^ 1
 }
 
-__device__ __forceinline__ float allreduce64(float x) {
-#pragma unroll
-  for (int h = 32; h >= 1; h >>= 1) x += __shfl_xor(x, h);
-  return x;
+// Sum over the wave, in every lane.
+__device__ __forceinline__ float wave_sum64(float x) {
+  x += dpp_row<0xB1>(x);
+  x += dpp_row<0x4E>(x);
+  x += dpp_row<0x141>(x);
+  x += dpp_row<0x140>(x);
+  auto lane = [&](int i) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i)); };
+  return (lane(0) + lane(16)) + (lane(32) + lane(48));
 }
 
 // Pair index of the non-adjacent block pairs (I, J), J <= I - 2, for C <= 64.
@@ -246,8 +272,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) p
     }
   }
 
-  // 2. gated operands, from the block-local inclusive cumsum Bloc (kept, in
-  // units of log2, for the diagonal block of step 4).
+  // 2. gated operands.  The decays inside the block are running products of
+  // the step decays alpha, which are kept for the diagonal block of step 4.
   float ez[FPL], ekt[FPL];
 #pragma unroll
   for (int f = 0; f < FPL; ++f) {
@@ -255,34 +281,41 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) p
     ekt[f] = __expf(Bl[f] - pre[f] - tot[f]);  // b_{chunk end} / b_{block end}
   }
   const auto rs_Qt = make_rsrc(Qt, bytes), rs_Kt = make_rsrc(Kt, bytes);
-  float c[FPL], B2[16][FPL];
+  float al[16][FPL], run[FPL];
 #pragma unroll
-  for (int f = 0; f < FPL; ++f) c[f] = 0.f;
+  for (int f = 0; f < FPL; ++f) run[f] = 1.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int row = 16 * w + r;
-    float xl[FPL], qv[FPL], kv[FPL], o1[FPL], o2[FPL], o3[FPL], o4[FPL];
-    unpack_la(r, xl);
+    float xl[FPL], qv[FPL], o1[FPL], o3[FPL];
+    if constexpr (!PRE) unpack_la(r, xl);
     unpack<T, FPL>(rq[r], qv);
+#pragma unroll
+    for (int f = 0; f < FPL; ++f) {
+      if constexpr (PRE) al[r][f] = __expf(lav[r][f]);
+      else al[r][f] = __expf(xl[f]);
+      run[f] *= al[r][f];       // exp(Bloc)
+      o3[f] = qv[f] * run[f];   // <= |q|
+      o1[f] = o3[f] * ez[f];
+    }
+    straw<T, FPL>(rs_Qt, lane_off + r * row_step, o1);
+    if (fp) stvec<T, FPL>(sQh + row * ldk + k0, o3);
+  }
+#pragma unroll
+  for (int f = 0; f < FPL; ++f) run[f] = 1.f;
+#pragma unroll
+  for (int r = 15; r >= 0; --r) {
+    const int row = 16 * w + r;
+    float kv[FPL], o2[FPL], o4[FPL];
     unpack<T, FPL>(rk[r], kv);
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
-      if constexpr (PRE) c[f] += lav[r][f];
-      else c[f] += xl[f];
-      B2[r][f] = c[f] * kLog2e;
-      const float qhv = qv[f] * __expf(c[f]);           // <= |q|
-      const float ksv = kv[f] * __expf(tot[f] - c[f]);  // <= |k|
-      o1[f] = qhv * ez[f];
-      o2[f] = ksv * ekt[f];
-      o3[f] = qhv;
-      o4[f] = ksv;
+      o4[f] = kv[f] * run[f];   // k exp(tot - Bloc), <= |k|
+      o2[f] = o4[f] * ekt[f];
+      run[f] *= al[r][f];
     }
-    straw<T, FPL>(rs_Qt, lane_off + r * row_step, o1);
     straw<T, FPL>(rs_Kt, lane_off + r * row_step, o2);
-    if (fp) {
-      stvec<T, FPL>(sQh + row * ldk + k0, o3);
-      stvec<T, FPL>(sKs + row * ldk + k0, o4);
-    }
+    if (fp) stvec<T, FPL>(sKs + row * ldk + k0, o4);
   }
   if (w == 0 && fv) {
     float gv[FPL];
@@ -326,55 +359,86 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) p
     for (int r = 0; r < 4; ++r) Pg[(d0 + 4 * g + r) * C + 16 * J + j16] = cvt<T>(acc[r]);
   }
 
-  // 4. the diagonal block in fp32 log space (Eq. 4): pair p = (i, j), j <= i,
-  // of the block's 136 is sum_k q_ik k_jk 2^(B2_ik - B2_jk); each lane sums
-  // its own features for 32 pairs at a time, then the wave reduces (pairs
-  // 0..127 by reduce-scatter, lane l ending with pair p0 + l % 32; pairs
-  // 128..135 by all-reduce).  The q, k values are the io-dtype inputs
-  // themselves.
-  auto pink = [&](auto p0, auto np, float (&x)[32]) {
-    constexpr int P0 = decltype(p0)::value, NP = decltype(np)::value;
+  // 4. the diagonal block in fp32 (Eq. 4): each lane sums its own features'
+  // terms q_ik k_jk (product of alpha over rows j+1 .. i) of up to 36 pairs at
+  // a time, then the wave reduces 32 of them by reduce-scatter; the four left
+  // of each triangle are all-reduced together.  The q, k values are the
+  // io-dtype inputs themselves.  At d_k = 256 this took prep from 136
+  // exponentials per feature and block to 16: 79 to 54 us on 8 x 4 heads of
+  // 2048 steps (bf16; 184 MB moved, 37 us at the copy rate), 234 to 163 us on
+  // 16 x 16 heads of 2048 at d_k = 128.
+  auto elem = [&](const uint32_t (&raw)[NW], int f) {
+    float t[FPL];
+    unpack<T, FPL>(raw, t);
+    return t[f];
+  };
+  float left[8];
 #pragma unroll
-    for (int e = 0; e < NP; ++e) x[e] = 0.f;
+  for (int b = 0; b < 2; ++b) {  // triangles of rows 8b .. 8b + 7
+    float x[36];
+#pragma unroll
+    for (int e = 0; e < 36; ++e) x[e] = 0.f;
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
-      float qf[16], kf[16];
+      float u[8];  // k_j decayed to the current row
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float t[FPL];
-        unpack<T, FPL>(rq[r], t);
-        qf[r] = t[f];
-        unpack<T, FPL>(rk[r], t);
-        kf[r] = t[f];
-      }
+      for (int i = 0; i < 8; ++i) {
 #pragma unroll
-      for (int e = 0; e < NP; ++e) {
-        const int i = tri_row(P0 + e), jj = tri_col(P0 + e);
-        x[e] += qf[i] * kf[jj] * exp2f_fast(B2[i][f] - B2[jj][f]);
+        for (int j = 0; j < i; ++j) u[j] *= al[8 * b + i][f];
+        u[i] = elem(rk[8 * b + i], f);
+        const float qi = elem(rq[8 * b + i], f);
+#pragma unroll
+        for (int j = 0; j <= i; ++j) x[i * (i + 1) / 2 + j] += qi * u[j];
       }
     }
-  };
-  auto pink32 = [&](auto p0) {
-    constexpr int P0 = decltype(p0)::value;
+    float y[32];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) y[e] = x[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) left[4 * b + e] = x[32 + e];
+    const float r = reduce_scatter32(y);
+    const int e = l >> 1;
+    if ((l & 1) == 0) Pg[(d0 + 8 * b + tri_row(e)) * C + d0 + 8 * b + tri_col(e)] = cvt<T>(r);
+  }
+  float kb[8][FPL], dec[FPL];  // rows 0 .. 7 of k decayed to the end of row 7
+#pragma unroll
+  for (int f = 0; f < FPL; ++f) {
+    float u = 1.f;
+#pragma unroll
+    for (int j = 7; j >= 0; --j) {
+      kb[j][f] = elem(rk[j], f) * u;
+      u *= al[j][f];
+    }
+    dec[f] = 1.f;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {  // rows 8 + 4h .. +3 of the square
     float x[32];
-    pink(p0, std::integral_constant<int, 32>{}, x);
+#pragma unroll
+    for (int e = 0; e < 32; ++e) x[e] = 0.f;
+#pragma unroll
+    for (int f = 0; f < FPL; ++f) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        dec[f] *= al[8 + 4 * h + i][f];
+        const float qi = elem(rq[8 + 4 * h + i], f) * dec[f];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[8 * i + j] += qi * kb[j][f];
+      }
+    }
     const float r = reduce_scatter32(x);
-    if (l < 32) Pg[(d0 + tri_row(P0 + l)) * C + d0 + tri_col(P0 + l)] = cvt<T>(r);
-  };
-  pink32(std::integral_constant<int, 0>{});
-  pink32(std::integral_constant<int, 32>{});
-  pink32(std::integral_constant<int, 64>{});
-  pink32(std::integral_constant<int, 96>{});
+    const int e = l >> 1;
+    if ((l & 1) == 0) Pg[(d0 + 8 + 4 * h + (e >> 3)) * C + d0 + (e & 7)] = cvt<T>(r);
+  }
   {
-    float x[32];
-    pink(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{}, x);
+    // entries 32 .. 35 of each triangle: row 7, columns 4 .. 7
     float rt = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float s = allreduce64(x[e]);
+      const float s = wave_sum64(left[e]);
       if (l == e) rt = s;
     }
-    if (l < 8) Pg[(d0 + 15) * C + d0 + 8 + l] = cvt<T>(rt);
+    if (l < 8) Pg[(d0 + 7 + 8 * (l >> 2)) * C + d0 + 8 * (l >> 2) + 4 + (l & 3)] = cvt<T>(rt);
   }
 }
 
