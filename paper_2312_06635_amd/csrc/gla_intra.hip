@@ -19,8 +19,9 @@
 //   1. The chunk's dP (fp32, masked, stored transposed) into LDS.
 //   2. For each group of 64 key features (lane = feature):
 //      - gate cumsums of the wave's block; the sub-chunk ("pink") diagonal
-//        block in fp32 log space on the vector ALUs: one exponential
-//        2^(B2_i - B2_j) per pair, shared by the dq and dk sums;
+//        block in fp32 on the vector ALUs, the decay of a pair formed as the
+//        product of the step decays between its rows (one exponential per
+//        row), shared by the dq and dk sums;
 //      - the blocks between sub-chunks ("orange") on the matrix cores: with
 //        normalisers at block boundaries every exponent is <= 0,
 //          dq_I = exp(Bloc_I) (.) sum_{J<I} g_IJ (.) dP_IJ (k_J (.) exp(tot_J - Bloc_J))
@@ -217,12 +218,12 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, fv ? (uint32_t)(((16 * w + r) * K + f) * 4) : 0x80000000u, 0, 0);
-    float q[16], kk[16], c[16];
+    float q[16], kk[16], c[16], la[PRE ? 16 : 1];
     float run = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float x = el_f<T>(rl[r]);
-      if constexpr (PRE) x = gate_la(x, a.inv_tau, fv && 16 * w + r < rv);
+      if constexpr (PRE) la[r] = x = gate_la(x, a.inv_tau, fv && 16 * w + r < rv);
       run += x;
       c[r] = run;  // Bloc
       q[r] = el_f<T>(rq[r]);
@@ -246,14 +247,14 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
       *(f4 *)(sKz + l * LDD + 16 * w + r) = kz;
     }
 
-    // pink: the diagonal block in fp32 log space, one exponential per pair
-    // shared by both sums (dP rows read as wave-uniform broadcasts)
-    float dqp[16], dkp[16], c2[16];
+    // pink: the diagonal block in fp32, the decay of a pair (i, j) carried from
+    // row to row as the product of the step decays (dec[j] at row i), shared
+    // by both sums (dP rows read as wave-uniform broadcasts).  One exponential
+    // per row instead of one per pair: 339 to 304 us on 16 x 16 heads of 2048
+    // steps at d_k = 128, 94 to 89 us on 8 x 4 heads at d_k = 256 (bf16).
+    float dqp[16], dkp[16], dec[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      dqp[r] = dkp[r] = 0.f;
-      c2[r] = c[r] * kLog2e;
-    }
+    for (int r = 0; r < 16; ++r) dqp[r] = dkp[r] = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float *prow = sdP + (16 * w + i) * LDD + 16 * w;
@@ -264,15 +265,22 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int u = 0; u < 4; ++u) p[4 * j4 + u] = v4[u];
       }
+      float x = el_f<T>(rl[i]);
+      if constexpr (PRE) x = la[i];
+      const float al = __expf(x);
 #pragma unroll
-      for (int j = 0; j <= i; ++j) {
-        const float t = p[j] * exp2f_fast(c2[i] - c2[j]);
+      for (int j = 0; j < i; ++j) {
+        dec[j] *= al;
+        const float t = p[j] * dec[j];
         dqp[i] += t * kk[j];
         dkp[j] += t * q[i];
       }
+      dec[i] = 1.f;
+      dqp[i] += p[i] * kk[i];
+      dkp[i] += p[i] * q[i];
     }
-    // finish the sums here: sunk to their use after the orange blocks, the 136
-    // exponentials would all stay live across them
+    // finish the sums here: sunk to their use after the orange blocks, their
+    // terms would all stay live across them
 #pragma unroll
     for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(dqp[r]), "+v"(dkp[r]));
     __syncthreads();  // B2: group tiles complete
