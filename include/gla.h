@@ -113,7 +113,7 @@ enum {
    * sum over the key features of the per-feature gate gradient (summed in a
    * fixed order: reproducible bits).  Combines with gate_tau (z then [B, H, T]:
    * gamma = sigmoid(z)^(1/tau), Gated Retention; tau = 1, mLSTM).  Every entry
-   * point honours it, gla_workspace_bytes included (the backward then needs
+   * point honours it, gla_workspace_bytes included (the backward then asks for
    * B H ceil(d_k/32) T fp32 more). */
   GLA_FLAG_SCALAR_GATE = 1u << 1,
   /* Accepted for compatibility and without effect: every diagonal (within
@@ -129,11 +129,11 @@ enum {
    *   gla_chunk_fwd: 1 = gate factors, gated operands and intra-chunk P
    *                  2 = state pass and chunk outputs
    *   gla_chunk_bwd: 1 = as forward stage 1 (skipped with REUSE_FWD_WORKSPACE)
-   *                  2 = forward sweep over key-feature tiles: dq_inter
-   *                      (and dP = (dO V^T) (.) M)
-   *                  3 = intra-chunk terms, chunk-parallel: dq, and dk_intra
-   *                      and its share of the gate gradient for stage 4
-   *                  4 = reverse sweep over key-feature tiles: dk, dlog_alpha
+   *                  2 = the sweeps over key-feature tiles, forward and
+   *                      reverse side by side: dq_inter, dk_inter (and dP =
+   *                      (dO V^T) (.) M)
+   *                  3 = in-chunk terms, chunk-parallel: dq, dk, dlog_alpha
+   *                  4 = nothing (its work is in stages 2 and 3)
    *                  5 = reverse sweep over value-column tiles: dv, dS0
    * Out-of-range stage numbers return GLA_ERR_SHAPE. */
   GLA_STAGE_SHIFT = 8,
@@ -258,7 +258,7 @@ gla_status gla_recurrent_fwd_general(const gla_problem *prob, const void *q, con
  * the gate epilogue (gate_tau > 0: GLA_ERR_UNSUPPORTED).  Workspace: at least
  * gla_workspace_bytes(prob, 2) bytes; GLA_FLAG_REUSE_FWD_WORKSPACE as for
  * gla_chunk_bwd.  Stage selector: 1 = key-gate factors (as gla_chunk_bwd),
- * 2 = value-gate operands, 3 = dq sweep, 4 = intra-chunk terms, 5 = dk sweep,
+ * 2 = value-gate operands, 3 = the key sweeps, 4 = in-chunk terms, 5 = nothing,
  * 6 = dv sweep, 7 = the value-gate gradient. */
 gla_status gla_chunk_bwd_general(const gla_problem *prob, const void *q, const void *k, const void *v,
                                  const void *log_alpha, const void *log_beta, const float *S0, const void *o,

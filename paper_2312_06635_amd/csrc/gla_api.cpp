@@ -56,8 +56,7 @@ bool lds_bad(size_t bytes) { return bytes == 0 || bytes > gla::kMaxLds; }
 
 gla_status check_lds(const Shape &s, bool bwd) {
   if (lds_bad(gla::lds_prep(s)) || lds_bad(gla::lds_fwd_main(s))) return GLA_ERR_UNSUPPORTED;
-  if (bwd && (lds_bad(gla::lds_bwd_intra(s)) || lds_bad(gla::lds_bwd_dq(s)) || lds_bad(gla::lds_bwd_dk(s)) ||
-              lds_bad(gla::lds_bwd_dv(s))))
+  if (bwd && (lds_bad(gla::lds_bwd_intra(s)) || lds_bad(gla::lds_key_sweeps(s)) || lds_bad(gla::lds_bwd_dv(s))))
     return GLA_ERR_UNSUPPORTED;
   return GLA_OK;
 }
@@ -133,31 +132,33 @@ size_t layout(const Shape &s, int op, char *base, Work *w, int nseg) {
     Sloc = take(states);
     dec = take((size_t)s.BH * s.K * sizeof(float));
   }
-  void *dP = nullptr, *dki = nullptr, *dai = nullptr, *dat = nullptr, *dqr = nullptr;
-  void *cST = nullptr, *dla_part = nullptr;
-  void *Vh = nullptr, *Oh = nullptr, *gb = nullptr, *Sb = nullptr, *cpart = nullptr;
+  void *dP = nullptr, *dqr = nullptr, *dkr = nullptr, *tq = nullptr, *tk = nullptr, *cST = nullptr, *carry = nullptr;
+  void *Vh = nullptr, *Oh = nullptr, *gb = nullptr, *Sb = nullptr, *Db = nullptr, *cpart = nullptr;
   if (op >= 1) {
     dP = take(chunks * s.C * s.C * sizeof(float));
-    dki = take(rows * s.K * es);
-    dai = take(rows * s.K * es);
-    dat = take(chunks * s.K * sizeof(float));
     dqr = take(rows * s.K * sizeof(float));
+    dkr = take(rows * s.K * sizeof(float));
+    tq = take(chunks * s.K * sizeof(float));
+    tk = take(chunks * s.K * sizeof(float));
+    carry = take(chunks * s.K * sizeof(float));
     cST = take((size_t)s.BH * s.K * sizeof(float));
-    if (s.sgate) dla_part = take(rows * ((s.K + 31) / 32) * sizeof(float));
+    // (scalar gates: the documented extra bytes stay part of the size)
+    if (s.sgate) take(rows * ((s.K + 31) / 32) * sizeof(float));
     if (nseg > 1) dSout = take(states);
   }
   if (op == 2) {
     Vh = take(rows * s.V * es);
     Oh = take(rows * s.V * es);
     gb = take(chunks * s.V * sizeof(float));
-    Sb = take(gla::ks_state_bytes(s));
-    cpart = take(chunks * ((s.K + 31) / 32) * s.V * sizeof(float));
+    Sb = take(gla::ks_state_elems(s) * es);
+    Db = take(gla::ks_state_elems(s) * sizeof(float));
+    cpart = take(chunks * s.V * sizeof(float));
   }
   if (w) {
     w->Qt = Qt; w->Kt = Kt; w->P = P; w->gam = (float *)gam;
-    w->dP = (float *)dP; w->dki = dki; w->dai = dai; w->dat = (float *)dat; w->dqr = (float *)dqr;
-    w->cST = (float *)cST; w->dla_part = (float *)dla_part;
-    w->Vh = Vh; w->Oh = Oh; w->gb = (float *)gb; w->Sb = Sb; w->cpart = (float *)cpart;
+    w->dP = (float *)dP; w->dqr = (float *)dqr; w->dkr = (float *)dkr; w->tq = (float *)tq; w->tk = (float *)tk;
+    w->cST = (float *)cST; w->carry = (float *)carry;
+    w->Vh = Vh; w->Oh = Oh; w->gb = (float *)gb; w->Sb = Sb; w->Db = (float *)Db; w->cpart = (float *)cpart;
     w->Sin = (float *)Sin; w->Sloc = (float *)Sloc; w->dec = (float *)dec; w->dSout = (float *)dSout;
   }
   return off;
@@ -328,11 +329,10 @@ GLA_EXPORT gla_status gla_chunk_bwd(const gla_problem *prob, const void *q, cons
       if (e == hipSuccess)
         e = gla::launch_seg_bwd_scan(s.BH, nseg, s.K, s.V, w.dec, dS_T, w.Sloc, w.dSout, dS0, hs);
     }
-    if (e == hipSuccess) e = gla::launch_bwd_dq(s2, k, log_alpha, v, S0s, dO, dSTs, w, hs, ng);
+    if (e == hipSuccess) e = gla::launch_key_sweeps(s2, q, k, log_alpha, v, S0s, dO, dSTs, w, hs, ng);
   }
-  if (e == hipSuccess && run(3)) e = gla::launch_bwd_intra(s2, q, k, log_alpha, dq, w, hs, ng);
-  if (e == hipSuccess && run(4))
-    e = gla::launch_bwd_dk(s2, q, k, log_alpha, v, dO, dSTs, dq, dk, dlog_alpha, w, hs);
+  if (e == hipSuccess && run(3))
+    e = gla::launch_bwd_intra(s, nseg, q, k, log_alpha, dSTs != nullptr, dq, dk, dlog_alpha, w, hs, ng);
   if (e == hipSuccess && run(5)) e = gla::launch_bwd_dv(s2, dO, nullptr, dSTs, dv, nseg > 1 ? nullptr : dS0, w, hs);
   return hip_status(e);
 }
@@ -368,10 +368,9 @@ GLA_EXPORT gla_status gla_chunk_bwd_general(const gla_problem *prob, const void 
   if (run(1) && !(prob->flags & GLA_FLAG_REUSE_FWD_WORKSPACE))
     e = gla::launch_prep(s, q, k, log_alpha, w, hs);
   if (e == hipSuccess && run(2)) e = gla::launch_beta_prep(s, v, dO, log_beta, w, hs);
-  if (e == hipSuccess && run(3)) e = gla::launch_bwd_dq(s, k, log_alpha, w.Vh, S0, w.Oh, dS_T, w, hs, false, true);
-  if (e == hipSuccess && run(4)) e = gla::launch_bwd_intra(s, q, k, log_alpha, dq, w, hs, false);
-  if (e == hipSuccess && run(5))
-    e = gla::launch_bwd_dk(s, q, k, log_alpha, w.Vh, w.Oh, dS_T, dq, dk, dlog_alpha, w, hs, true);
+  if (e == hipSuccess && run(3)) e = gla::launch_key_sweeps(s, q, k, log_alpha, w.Vh, S0, w.Oh, dS_T, w, hs, false, true);
+  if (e == hipSuccess && run(4))
+    e = gla::launch_bwd_intra(s, 1, q, k, log_alpha, dS_T != nullptr, dq, dk, dlog_alpha, w, hs, false);
   if (e == hipSuccess && run(6)) e = gla::launch_bwd_dv(s, dO, log_beta, dS_T, dv, dS0, w, hs);
   if (e == hipSuccess && run(7) && dlog_beta)
     e = gla::launch_beta_grad(s, o, dO, v, dv, dlog_beta, w, hs);

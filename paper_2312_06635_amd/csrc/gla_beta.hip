@@ -4,8 +4,8 @@
 //     dlog beta_t = sum_{i >= t} (o_i (.) do_i - v_i (.) dv_i) + colsum(S_T (.) dS_T).
 // The part of that sum beyond chunk n equals colsum(S_[n+1] (.) dS_[n+1])
 // exactly (the state-form gate gradient at the next chunk's first step), so
-// the carry into each chunk comes from the chunk-end states (summed over the
-// key tiles by the dk sweep) and only the chunk's own rows are summed here:
+// the carry into each chunk comes from the chunk-end states and their
+// gradients (gla_ksweep.hip) and only the chunk's own rows are summed here:
 // no rounding accumulates over the sequence.
 // With E the chunk-local inclusive cumsum of log beta per value column,
 //     Vh = V (.) exp(-E),   Oh = dO (.) exp(E),   gb = exp(E_last) per chunk,
@@ -25,9 +25,9 @@ struct BetaArgs {
   const void *v, *dO, *lb, *o, *dv;
   void *Vh, *Oh, *dlb;
   float *gb;
-  const float *cpart;     // [BH][N][KT][V] per key tile colsum(S_[n+1] (.) dS_[n+1])
+  const float *cpart;     // [BH][N][V] colsum(S_[n+1] (.) dS_[n+1])
   int64_t n;              // BH N V threads
-  int T, V, C, N, KT;
+  int T, V, C, N;
 };
 
 struct Cell {
@@ -81,15 +81,13 @@ __global__ void __launch_bounds__(256) beta_prep_kernel(BetaArgs a) {
   a.gb[c.cn * a.V + c.col] = __expf(E);
 }
 
-// Reverse cumsum inside each chunk, starting from the chunk's carry (key
-// tiles added in order).
+// Reverse cumsum inside each chunk, starting from the chunk's carry.
 template <typename T>
 __global__ void __launch_bounds__(256) beta_grad_scan_kernel(BetaArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= a.n) return;
   const Cell c = cell_of(a, i);
-  float carry = 0.f;
-  for (int kt = 0; kt < a.KT; ++kt) carry += a.cpart[(c.cn * a.KT + kt) * a.V + c.col];
+  float carry = a.cpart[c.cn * a.V + c.col];
   const T *o = (const T *)a.o + c.base, *dO = (const T *)a.dO + c.base;
   const T *v = (const T *)a.v + c.base, *dv = (const T *)a.dv + c.base;
   T *dlb = (T *)a.dlb + c.base;
@@ -111,7 +109,7 @@ hipError_t beta_launch(int which, const BetaArgs &a, hipStream_t st) {
 BetaArgs beta_args(const Shape &s) {
   BetaArgs a{};
   a.n = (int64_t)s.BH * s.N * s.V;
-  a.T = s.T; a.V = s.V; a.C = s.C; a.N = s.N; a.KT = (s.K + 31) / 32;
+  a.T = s.T; a.V = s.V; a.C = s.C; a.N = s.N;
   return a;
 }
 

@@ -227,8 +227,9 @@ template <typename T, int ROWS, int COLS, int NT> struct TileLd {
 // the 8 XCDs, so when the head count is a multiple of 8 the tiles of one head
 // are all given ids with the same residue mod 8 (one XCD, one L2), letting
 // them share the head's per-chunk operands through that L2.
-__device__ __forceinline__ void xcd_map(int nheads, int ntiles, int &head, int &tile) {
-  const int id = blockIdx.x;
+// id: the workgroup's number among its kind (a multiple of 8 away from
+// blockIdx.x, or the mapping only loses its locality).
+__device__ __forceinline__ void xcd_map(int id, int nheads, int ntiles, int &head, int &tile) {
   if ((nheads & 7) == 0) {
     const int xcd = id & 7, s = id >> 3;
     tile = s % ntiles;

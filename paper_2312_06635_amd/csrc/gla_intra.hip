@@ -1,19 +1,22 @@
-// gla_intra.hip -- the intra-chunk part of the backward (App. B, Alg. 4/6 as
-// corrected in the header of gla_vsweep.hip), chunk-parallel: none of it
-// depends on the states, so it is computed once per (head, chunk) here and
-// the key sweeps keep only the state recurrences.
+// gla_intra.hip -- the chunk-parallel part of the backward (App. B, Alg. 4/6 as
+// corrected in the header of gla_vsweep.hip): the intra-chunk terms, which
+// depend on no state, and with the key sweeps' inter-chunk terms the
+// gradients themselves.
 //
 // Per chunk (rows t of the chunk, B = chunk-local inclusive cumsum of log
 // alpha, dP = (dO V^T) (.) M):
 //   dq_intra[i] = sum_{j <= i} dP_ij k_j (.) exp(B_i - B_j)
 //   dk_intra[j] = sum_{i >= j} dP_ij q_i (.) exp(B_i - B_j)
-//   dA_intra[t] = q_t (.) dq_intra[t] - k_t (.) dk_intra[t]   (Sec. 4.3)
-// It runs between the key sweeps: it writes dq = dq_inter + dq_intra (the dq
-// sweep's fp32 dq_inter in), and for the dk sweep dk_intra, the in-chunk
-// reverse cumsum of dA_intra (io dtype: each is added once to an fp32
-// inter-chunk term) and the chunk total of dA_intra (fp32: the gate gradient
-// carries it across chunks).  dP comes from the dq sweep, which streams V and
-// dO anyway.
+//   dq = dq_inter + dq_intra,  dk = dk_inter + dk_intra
+//   dlog alpha_t = sum_{i >= t, in the chunk} (q_i (.) dq_i - k_i (.) dk_i) + carry_n   (Sec. 4.3)
+// The carry into chunk n is what the later chunks' rows add, and the
+// final-state term rowsum(S_T (.) dS_T).  Summed over a whole chunk the intra
+// terms cancel (both sums are sum_ij dP_ij q_i k_j exp(B_i - B_j) per feature),
+// so a later chunk m adds the sums of q (.) dq_inter and k (.) dk_inter that the
+// key sweeps leave per chunk, tq_m - tk_m.  The waves add them here (up to
+// kCarryDirect chunks: a quarter of the rows each, all loads independent), or
+// carry_scan_kernel forms every chunk's carry beforehand.  Everything of the
+// gate gradient stays fp32 up to the one rounding of the result.
 //
 // One workgroup per (chunk, head), wave w = the 16-row block w of the chunk.
 //   1. The chunk's dP (fp32, masked, stored transposed) into LDS.
@@ -30,8 +33,11 @@
 //        blocks strictly between J and I), the fp32 operands split into bf16
 //        hi + lo (three products) so that the gate gradient keeps fp32
 //        accuracy;
-//      - per (row, feature): the two parts added, dA formed and summed
-//        backwards over the chunk.
+//      - per (row, feature): the parts added, dq and dk written, q (.) dq -
+//        k (.) dk summed backwards over the chunk.
+// The traffic is q, k, the gate, dq_inter and dk_inter (fp32) and dP in, dq, dk
+// and the gate gradient out: 369 MB on 8 x 4 heads of 2048 steps at d_k = 256
+// in bf16, 75 us at the copy rate; measured 97-103 us.
 #include <type_traits>
 
 #include "gla_common.hpp"
@@ -41,18 +47,33 @@ namespace gla {
 
 namespace {
 
+constexpr int kCarryDirect = 64;  // chunks per sequence up to which the carry is summed in place
+
 struct IntraArgs {
   const void *q, *k, *la;
-  const float *dP;        // [BH][N][C][C] fp32, transposed ([s][t])
-  const float *dqr;       // [BH][T][K] fp32 dq_inter
-  void *dq;               // [BH][T][K] io: the layer's dq
-  void *dki, *dai;        // [BH][T][K] io
-  float *dat;             // [BH][N][K] fp32
+  const float *dP;          // [BH][N][C][C] fp32, transposed ([s][t])
+  const float *dqr, *dkr;   // [BH][T][K] fp32 dq_inter, dk_inter
+  const float *tq, *tk;     // [BH][N][K] fp32 chunk sums of q (.) dq_inter, k (.) dk_inter
+  const float *cST;         // [BH nseg][K] fp32 final-state terms, or NULL
+  const float *carry;       // [BH][N][K] fp32 carries already formed, or NULL
+  void *dq, *dk;            // [BH][T][K] io
+  void *dla;                // [BH][T][K] io ([BH][T] for a scalar gate), nullable
   int T, K, C, N;
-  int sg;         // scalar gate: la is [BH][T]
-  int ng;         // no gate and no gate gradient
+  int nseg, Ns;   // segments per head, chunks per segment (each segment's last chunk starts from its own cST)
+  int sg;         // scalar gate: la and dla are [BH][T]
   float inv_tau;  // gate epilogue (0: la holds log alpha)
 };
+
+// This wave's share of the carry into chunk n: the later chunks' sums, every
+// NB-th row from n + 1 + w (wave 0 also the final-state term).
+template <int NB> __device__ __forceinline__ float carry_part(const IntraArgs &a, int bh, int n, int f, int w) {
+  const int64_t c0 = (int64_t)bh * a.N;
+  if (a.carry) return w == 0 ? a.carry[(c0 + n) * a.K + f] : 0.f;
+  const int seg = n / a.Ns, end = min((seg + 1) * a.Ns, a.N);
+  float s = (w == 0 && a.cST) ? a.cST[((int64_t)bh * a.nseg + seg) * a.K + f] : 0.f;
+  for (int m = n + 1 + w; m < end; m += NB) s += a.tq[(c0 + m) * a.K + f] - a.tk[(c0 + m) * a.K + f];
+  return s;
+}
 
 template <typename T> __device__ __forceinline__ uint32_t ld_el(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   if constexpr (sizeof(T) == 2) return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
@@ -67,6 +88,13 @@ template <typename T> __device__ __forceinline__ void st_el(__amdgpu_buffer_rsrc
     __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, cvt<bf16>(x)), rs, off, 0, 0);
   else
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rs, off, 0, 0);
+}
+
+// Sum over the wave, in every lane.
+__device__ __forceinline__ float wave_sum64(float x) {
+#pragma unroll
+  for (int h = 32; h >= 1; h >>= 1) x += __shfl_xor(x, h);
+  return x;
 }
 
 // acc += a b for fp32 operands: on the bf16 path both are split into hi + lo
@@ -131,7 +159,8 @@ template <int C> struct IntraLayout {
   static constexpr size_t offdP = 0;                                   // [C][LDD] fp32
   static constexpr size_t offTot = offdP + 4 * C * LDD;                // [NB][64] block sums of log alpha
   static constexpr size_t offTA = offTot + 4 * NB * 64;                // [NB][64] block sums of dA
-  static constexpr size_t offQz = offTA + 4 * NB * 64;                 // [64][LDD] q (.) exp(Bloc)
+  static constexpr size_t offCar = offTA + 4 * NB * 64;                // [NB][64] shares of the carry
+  static constexpr size_t offQz = offCar + 4 * NB * 64;                // [64][LDD] q (.) exp(Bloc)
   static constexpr size_t offKz = offQz + 4 * 64 * LDD;                // [64][LDD] k (.) exp(tot - Bloc)
   static constexpr size_t offO = offQz;                                // (aliased) [NB][2][64][LDO]
   static constexpr size_t total = offKz + 4 * 64 * LDD;
@@ -144,7 +173,7 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
   constexpr int NB = L::NB, LDD = L::LDD, LDO = L::LDO;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float *sdP = (float *)(smem + L::offdP);
-  float *sTot = (float *)(smem + L::offTot), *sTA = (float *)(smem + L::offTA);
+  float *sTot = (float *)(smem + L::offTot), *sTA = (float *)(smem + L::offTA), *sCar = (float *)(smem + L::offCar);
   float *sQz = (float *)(smem + L::offQz), *sKz = (float *)(smem + L::offKz);
   float *sO = (float *)(smem + L::offO);
 
@@ -156,21 +185,19 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 
   // ---- inputs of the feature groups (lane = feature): the group's rows of
   // q, k and the gate
-  const int lrow = a.sg ? 1 : K;  // gate elements per step
   const T *qc = (const T *)a.q + ((int64_t)bh * T_ + t0) * K;
   const T *kc = (const T *)a.k + ((int64_t)bh * T_ + t0) * K;
-  const uint32_t kbytes = rsrc_bytes((int64_t)(T_ - t0) * K * esz);
+  const uint32_t kbytes = rsrc_bytes((int64_t)(T_ - t0) * K * esz), fbytes = rsrc_bytes((int64_t)(T_ - t0) * K * 4);
   const auto rs_q = make_rsrc(qc, kbytes), rs_k = make_rsrc(kc, kbytes);
-  // an absent gate (alpha = 1) reads as log alpha = 0 from an empty range
-  const auto rs_la = make_rsrc(a.la ? (const T *)a.la + ((int64_t)bh * T_ + t0) * lrow : qc,
-                               a.la ? rsrc_bytes((int64_t)(T_ - t0) * lrow * esz) : 0u);
+  const auto rs_la = make_rsrc((const T *)a.la + ((int64_t)bh * T_ + t0) * K, kbytes);
   const auto rs_dq = make_rsrc((T *)a.dq + ((int64_t)bh * T_ + t0) * K, kbytes);
-  const auto rs_dki = make_rsrc((T *)a.dki + ((int64_t)bh * T_ + t0) * K, kbytes);
-  const auto rs_dai = make_rsrc((T *)a.dai + ((int64_t)bh * T_ + t0) * K, kbytes);
-  float *datc = a.dat + ((int64_t)bh * a.N + n) * K;
+  const auto rs_dk = make_rsrc((T *)a.dk + ((int64_t)bh * T_ + t0) * K, kbytes);
+  // an unwanted gate gradient is dropped through an empty range
+  const auto rs_dla = make_rsrc(a.dla ? (T *)a.dla + ((int64_t)bh * T_ + t0) * K : (T *)a.dq, a.dla ? kbytes : 0u);
+  const auto rs_dqr = make_rsrc(a.dqr + ((int64_t)bh * T_ + t0) * K, fbytes);
+  const auto rs_dkr = make_rsrc(a.dkr + ((int64_t)bh * T_ + t0) * K, fbytes);
   const int NG = (K + 63) / 64;
 
-  const auto rs_dqr = make_rsrc(a.dqr + ((int64_t)bh * T_ + t0) * K, rsrc_bytes((int64_t)(T_ - t0) * K * 4));
   uint32_t nq[16], nk[16], nl[16];
   auto issue_group = [&](int gi) {
     const int f = 64 * gi + l;
@@ -181,7 +208,7 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
       const uint32_t off = fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u;
       nq[r] = ld_el<T>(rs_q, off);
       nk[r] = ld_el<T>(rs_k, off);
-      nl[r] = ld_el<T>(rs_la, a.sg ? (fv ? (uint32_t)(row * esz) : 0x80000000u) : off);
+      nl[r] = ld_el<T>(rs_la, off);
     }
   };
 
@@ -206,7 +233,7 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
     const int f = 64 * gi + l;
     const bool fv = f < K;
     // the block's rows of q, k and the gate, for this lane's feature
-    uint32_t rq[16], rk[16], rl[16], rr[16];
+    uint32_t rq[16], rk[16], rl[16], rr[16], rs[16];
     issue_group(gi);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -214,10 +241,7 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
       rk[r] = nk[r];
       rl[r] = nl[r];
     }
-    // dq_inter of this group's rows: needed only at the combine
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, fv ? (uint32_t)(((16 * w + r) * K + f) * 4) : 0x80000000u, 0, 0);
+    if (fv) sCar[w * 64 + l] = carry_part<NB>(a, bh, n, f, w);
     float q[16], kk[16], c[16], la[PRE ? 16 : 1];
     float run = 0.f;
 #pragma unroll
@@ -283,6 +307,13 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
     // terms would all stay live across them
 #pragma unroll
     for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(dqp[r]), "+v"(dkp[r]));
+    // the inter-chunk terms of this group's rows: needed only at the combine
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t off = fv ? (uint32_t)(((16 * w + r) * K + f) * 4) : 0x80000000u;
+      rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, off, 0, 0);
+      rs[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dkr, off, 0, 0);
+    }
     __syncthreads();  // B2: group tiles complete
 
     // orange on the matrix cores: wave w forms dq for row block I = w and dk
@@ -354,11 +385,11 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 16 * w + r;
-      const float dq = __expf(c[r]) * oqw[l * LDO + r] + dqp[r];
-      const float dk = __expf(tot - c[r]) * okw[l * LDO + r] + dkp[r];
+      const float dq = __builtin_bit_cast(float, rr[r]) + (__expf(c[r]) * oqw[l * LDO + r] + dqp[r]);
+      const float dk = __builtin_bit_cast(float, rs[r]) + (__expf(tot - c[r]) * okw[l * LDO + r] + dkp[r]);
       const uint32_t off = fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u;
-      st_el<T>(rs_dq, off, __builtin_bit_cast(float, rr[r]) + dq);
-      st_el<T>(rs_dki, off, dk);
+      st_el<T>(rs_dq, off, dq);
+      st_el<T>(rs_dk, off, dk);
       dA[r] = q[r] * dq - kk[r] * dk;
     }
     float sa = 0.f;
@@ -371,14 +402,18 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
     __syncthreads();  // B4: block sums of dA published
     float later = 0.f;
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int b = 0; b < NB; ++b) {
+      if (fv) later += sCar[b * 64 + l];
       if (b > w) later += sTA[b * 64 + l];
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 16 * w + r;
-      st_el<T>(rs_dai, fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u, dA[r] + later);
+      float x = dA[r] + later;
+      if constexpr (PRE) x *= gate_dla_dg(el_f<T>(rl[r]), a.inv_tau);  // dL/dz = dL/dlog alpha * sigmoid(-z) / tau
+      st_el<T>(rs_dla, fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u, x);
     }
-    if (w == 0 && fv) datc[f] = sa + later;
+    __syncthreads();  // B5: the carry shares have been read
   }
 }
 
@@ -395,16 +430,16 @@ template <typename T> __device__ __forceinline__ f4 mma2s(f4 acc, const Split<T>
 //   dq_intra = dPD K,   dk_intra = dPD^T Q,
 // each one matrix-core product per 16x16 output tile and 32-row slab: dPD is
 // split into bf16 hi + lo once per chunk, q and k enter exactly (no
-// factorised operands, no per-feature exponentials).  The gate gradient's
-// parts (dai, dat) are formed as in the per-feature kernel; NG (no gate)
-// skips them.
+// factorised operands, no per-feature exponentials).  The gate gradient is
+// formed as in the per-feature kernel and, for a scalar gate, summed over the
+// features; NG (no gate) skips it.
 template <typename T, int C, bool PRE, bool NG>
 __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per_eu(2)))
 intra_plain_kernel(IntraArgs a) {
   using L = IntraLayout<C>;
   constexpr int NB = L::NB, LDD = L::LDD, LDO = L::LDO;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  float *sdP = (float *)(smem + L::offdP), *sTA = (float *)(smem + L::offTA);
+  float *sdP = (float *)(smem + L::offdP), *sTA = (float *)(smem + L::offTA), *sCar = (float *)(smem + L::offCar);
   float *sQz = (float *)(smem + L::offQz), *sKz = (float *)(smem + L::offKz);
   float *sO = (float *)(smem + L::offO);
 
@@ -418,17 +453,19 @@ intra_plain_kernel(IntraArgs a) {
   const uint32_t kbytes = rsrc_bytes((int64_t)(T_ - t0) * K * esz);
   const auto rs_q = make_rsrc(qc, kbytes), rs_k = make_rsrc(kc, kbytes);
   const auto rs_dq = make_rsrc((T *)a.dq + ((int64_t)bh * T_ + t0) * K, kbytes);
-  const auto rs_dki = make_rsrc((T *)a.dki + ((int64_t)bh * T_ + t0) * K, kbytes);
-  const auto rs_dqr = make_rsrc(a.dqr + ((int64_t)bh * T_ + t0) * K, rsrc_bytes((int64_t)(T_ - t0) * K * 4));
+  const auto rs_dk = make_rsrc((T *)a.dk + ((int64_t)bh * T_ + t0) * K, kbytes);
+  const uint32_t fbytes = rsrc_bytes((int64_t)(T_ - t0) * K * 4);
+  const auto rs_dqr = make_rsrc(a.dqr + ((int64_t)bh * T_ + t0) * K, fbytes);
+  const auto rs_dkr = make_rsrc(a.dkr + ((int64_t)bh * T_ + t0) * K, fbytes);
 
   // chunk-local inclusive cumsum of log gamma in units of log2, lane t = step t
-  float c2 = 0.f;
+  float c2 = 0.f, z = 0.f;  // (z: the gate argument of this lane's step)
   if constexpr (!NG) {
     // (an absent gate whose gradient is wanted reads as log alpha = 0 from an
     // empty range; the per-feature dA below is then that gradient's share)
     const auto rs_la = make_rsrc(a.la ? (const T *)a.la + (int64_t)bh * T_ + t0 : qc,
                                  a.la ? rsrc_bytes((int64_t)(T_ - t0) * esz) : 0u);
-    float x = el_f<T>(ld_el<T>(rs_la, l < C ? (uint32_t)(l * esz) : 0x80000000u));
+    float x = z = el_f<T>(ld_el<T>(rs_la, l < C ? (uint32_t)(l * esz) : 0x80000000u));
     if constexpr (PRE) x = gate_la(x, a.inv_tau, l < rv);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -486,10 +523,13 @@ intra_plain_kernel(IntraArgs a) {
 
   // ---- 2. feature groups (lane = feature)
   const int NGR = (K + 63) / 64;
+  float sum[16];  // scalar gate: this lane's features' gate gradient per row
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum[r] = 0.f;
   for (int gi = 0; gi < NGR; ++gi) {
     const int f = 64 * gi + l;
     const bool fv = f < K;
-    uint32_t rq[16], rk[16], rr[16];
+    uint32_t rq[16], rk[16], rr[16], rs[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const uint32_t off = fv ? (uint32_t)(((16 * w + r) * K + f) * esz) : 0x80000000u;
@@ -497,8 +537,14 @@ intra_plain_kernel(IntraArgs a) {
       rk[r] = ld_el<T>(rs_k, off);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, fv ? (uint32_t)(((16 * w + r) * K + f) * 4) : 0x80000000u, 0, 0);
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t off = fv ? (uint32_t)(((16 * w + r) * K + f) * 4) : 0x80000000u;
+      rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, off, 0, 0);
+      rs[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dkr, off, 0, 0);
+    }
+    if constexpr (!NG) {
+      if (fv) sCar[w * 64 + l] = carry_part<NB>(a, bh, n, f, w);
+    }
     float q[16], kk[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -564,14 +610,14 @@ intra_plain_kernel(IntraArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 16 * w + r;
-      const float dq = oqw[l * LDO + r], dk = okw[l * LDO + r];
+      const float dq = __builtin_bit_cast(float, rr[r]) + oqw[l * LDO + r];
+      const float dk = __builtin_bit_cast(float, rs[r]) + okw[l * LDO + r];
       const uint32_t off = fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u;
-      st_el<T>(rs_dq, off, __builtin_bit_cast(float, rr[r]) + dq);
-      st_el<T>(rs_dki, off, dk);
+      st_el<T>(rs_dq, off, dq);
+      st_el<T>(rs_dk, off, dk);
       dA[r] = q[r] * dq - kk[r] * dk;
     }
     if constexpr (!NG) {
-      const auto rs_dai = make_rsrc((T *)a.dai + ((int64_t)bh * T_ + t0) * K, kbytes);
       float sa = 0.f;
 #pragma unroll
       for (int r = 15; r >= 0; --r) {
@@ -582,16 +628,64 @@ intra_plain_kernel(IntraArgs a) {
       __syncthreads();  // block sums of dA published
       float later = 0.f;
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < NB; ++b) {
+        if (fv) later += sCar[b * 64 + l];
         if (b > w) later += sTA[b * 64 + l];
+      }
+      if (a.sg) {
+        // (features past d_k add q dq - k dk = 0 and no carry)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] += dA[r] + later;
+      } else {
+        // (no gate, its gradient wanted)
+        const auto rs_dla = make_rsrc(a.dla ? (T *)a.dla + ((int64_t)bh * T_ + t0) * K : (T *)a.dq, a.dla ? kbytes : 0u);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          st_el<T>(rs_dla, fv ? (uint32_t)(((16 * w + r) * K + f) * esz) : 0x80000000u, dA[r] + later);
+      }
+    }
+    __syncthreads();  // result tiles and carries consumed before the next group's overlay them
+  }
+  if constexpr (!NG) {
+    if (a.sg && a.dla) {
+      // the gate is shared by the features: its gradient is their sum, in a fixed order
+      float x = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = 16 * w + r;
-        st_el<T>(rs_dai, fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u, dA[r] + later);
+        const float t = wave_sum64(sum[r]);
+        if (l == r) x = t;
       }
-      if (w == 0 && fv) a.dat[((int64_t)bh * a.N + n) * K + f] = sa + later;
-    } else {
-      __syncthreads();  // result tiles consumed before the next group's tiles overlay them
+      const float zr = __shfl(z, 16 * w + (l & 15));
+      if constexpr (PRE) x *= gate_dla_dg(zr, a.inv_tau);
+      const auto rs_dla = make_rsrc((T *)a.dla + (int64_t)bh * T_ + t0, rsrc_bytes((int64_t)(T_ - t0) * esz));
+      st_el<T>(rs_dla, l < 16 ? (uint32_t)((16 * w + l) * esz) : 0x80000000u, x);
+    }
+  }
+}
+
+// carry[bh][n][k] of every chunk, for sequences of more than kCarryDirect
+// chunks: a thread owns one feature of one segment and walks its chunks
+// backwards, eight rows' loads at a time.
+__global__ void __launch_bounds__(64) carry_scan_kernel(IntraArgs a, float *carry) {
+  const int f = blockIdx.x * 64 + threadIdx.x, seg = blockIdx.y % a.nseg, bh = blockIdx.y / a.nseg;
+  if (f >= a.K) return;
+  const int beg = seg * a.Ns, end = min(beg + a.Ns, a.N);
+  const int64_t base = (int64_t)bh * a.N * a.K + f;
+  float s = a.cST ? a.cST[(int64_t)blockIdx.y * a.K + f] : 0.f;
+  for (int n1 = end; n1 > beg; n1 -= 8) {
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int64_t e = base + (int64_t)max(n1 - 1 - i, beg) * a.K;
+      x[i] = a.tq[e] - a.tk[e];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = n1 - 1 - i;
+      if (n >= beg) {
+        carry[base + (int64_t)n * a.K] = s;
+        s += x[i];
+      }
     }
   }
 }
@@ -616,8 +710,8 @@ hipError_t launch_intra_plain(const Shape &s, const IntraArgs &a, hipStream_t st
 }
 
 template <typename T, int C>
-hipError_t launch_intra_c(const Shape &s, const IntraArgs &a, hipStream_t st) {
-  if (a.ng) return launch_intra_plain<T, C, false, true>(s, a, st);
+hipError_t launch_intra_c(const Shape &s, const IntraArgs &a, hipStream_t st, bool ng) {
+  if (ng) return launch_intra_plain<T, C, false, true>(s, a, st);
   if (a.sg || !a.la)
     return a.inv_tau != 0.f ? launch_intra_plain<T, C, true, false>(s, a, st)
                             : launch_intra_plain<T, C, false, false>(s, a, st);
@@ -625,10 +719,10 @@ hipError_t launch_intra_c(const Shape &s, const IntraArgs &a, hipStream_t st) {
 }
 
 template <typename T>
-hipError_t launch_intra_io(const Shape &s, const IntraArgs &a, hipStream_t st) {
-  if (s.C == 16) return launch_intra_c<T, 16>(s, a, st);
-  if (s.C == 32) return launch_intra_c<T, 32>(s, a, st);
-  return launch_intra_c<T, 64>(s, a, st);
+hipError_t launch_intra_io(const Shape &s, const IntraArgs &a, hipStream_t st, bool ng) {
+  if (s.C == 16) return launch_intra_c<T, 16>(s, a, st, ng);
+  if (s.C == 32) return launch_intra_c<T, 32>(s, a, st, ng);
+  return launch_intra_c<T, 64>(s, a, st, ng);
 }
 
 }  // namespace
@@ -637,16 +731,25 @@ size_t lds_bwd_intra(const Shape &s) {
   return s.C == 16 ? IntraLayout<16>::total : (s.C == 32 ? IntraLayout<32>::total : IntraLayout<64>::total);
 }
 
-hipError_t launch_bwd_intra(const Shape &s, const void *q, const void *k, const void *la, void *dq, const Work &w,
-                            hipStream_t st, bool ng) {
-  IntraArgs a;
-  a.q = q; a.k = k; a.la = la; a.dP = w.dP; a.dqr = w.dqr; a.dq = dq;
-  a.dki = w.dki; a.dai = w.dai; a.dat = w.dat;
+hipError_t launch_bwd_intra(const Shape &s, int nseg, const void *q, const void *k, const void *la, bool has_dST,
+                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng) {
+  IntraArgs a{};
+  a.q = q; a.k = k; a.la = la; a.dP = w.dP; a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk;
+  a.cST = has_dST ? w.cST : nullptr;
+  a.dq = dq; a.dk = dk; a.dla = dla;
   a.T = s.T; a.K = s.K; a.C = s.C; a.N = s.N;
+  a.nseg = nseg; a.Ns = s.N / nseg;
   a.sg = s.sgate ? 1 : 0;
-  a.ng = ng ? 1 : 0;
   a.inv_tau = s.inv_tau;
-  return s.io == IO_BF16 ? launch_intra_io<bf16>(s, a, st) : launch_intra_io<float>(s, a, st);
+  if (!ng && dla && a.Ns > kCarryDirect) {
+    // (per workgroup the direct sum reads up to Ns rows of both arrays: beyond
+    // a few dozen that costs more than this pass over them)
+    hipLaunchKernelGGL(carry_scan_kernel, dim3((s.K + 63) / 64, s.BH * nseg), dim3(64), 0, st, a, w.carry);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.carry = w.carry;
+  }
+  return s.io == IO_BF16 ? launch_intra_io<bf16>(s, a, st, ng) : launch_intra_io<float>(s, a, st, ng);
 }
 
 }  // namespace gla

@@ -24,15 +24,14 @@ struct Work {
   void *Kt = nullptr;     // [BH][T][K] io : k (.) Gamma    (Gamma  = b_{chunk end} / b_t)
   void *P = nullptr;      // [BH][N][C][C] io : intra-chunk matrix, lower triangle
   float *gam = nullptr;   // [BH][N][K] fp32 : chunk decay gamma = b_{chunk end} / b_{chunk start}
-  // backward: the dq sweep's hand-offs and the intra-chunk terms (gla_intra.hip)
+  // backward: what the key sweeps hand to the in-chunk kernel (gla_intra.hip)
   float *dP = nullptr;    // [BH][N][C][C] fp32 : (dO V^T) (.) M per chunk, transposed ([s][t])
-  void *dki = nullptr;    // [BH][T][K] io : intra-chunk part of dk
-  void *dai = nullptr;    // [BH][T][K] io : in-chunk reverse cumsum of q dq_intra - k dk_intra
-  float *dat = nullptr;   // [BH][N][K] fp32 : its chunk totals
-  float *dqr = nullptr;   // [BH][T][K] fp32 : dq_inter (for dq and the gate gradient in the dk sweep)
-  float *cST = nullptr;   // [BH][K] fp32 : rowsum(S_T (.) dS_T) (backward)
-  float *dla_part = nullptr;  // [BH][ceil(K/32)][T] fp32 : per key tile sums of the gate
-                              //   gradient over its features (scalar gate only)
+  float *dqr = nullptr;   // [BH][T][K] fp32 : dq_inter
+  float *dkr = nullptr;   // [BH][T][K] fp32 : dk_inter
+  float *tq = nullptr;    // [BH][N][K] fp32 : per chunk sums of q (.) dq_inter
+  float *tk = nullptr;    // [BH][N][K] fp32 : per chunk sums of k (.) dk_inter
+  float *cST = nullptr;   // [BH][K] fp32 : rowsum(S_T (.) dS_T) (per segment)
+  float *carry = nullptr; // [BH][N][K] fp32 : gate gradient carried into each chunk (long sequences)
   // value-side gate of the general form (backward only; E = chunk-local
   // inclusive cumsum of log beta per value column)
   void *Vh = nullptr;         // [BH][T][V] io : V (.) exp(-E)
@@ -44,8 +43,9 @@ struct Work {
   float *Sloc = nullptr;      // [BH nseg][K][V] fp32 : local final states; then local dS0
   float *dec = nullptr;       // [BH nseg][K] fp32 : each segment's decay
   float *dSout = nullptr;     // [BH nseg][K][V] fp32 : each segment's final-state gradient
-  void *Sb = nullptr;         // chunk-end states S_[n+1] (io), written by the dq sweep (ks_state_bytes)
-  float *cpart = nullptr;     // [BH][N][ceil(K/32)][V] fp32 : per key tile colsum(S_[n+1] (.) dS_[n+1])
+  void *Sb = nullptr;         // chunk-end states S_[n+1] (io), written by the dq sweep (ks_state_elems)
+  float *Db = nullptr;        // their gradients dS_[n+1] (fp32), written by the dk sweep
+  float *cpart = nullptr;     // [BH][N][V] fp32 : colsum(S_[n+1] (.) dS_[n+1])
 };
 
 // Returns hipSuccess or the launch error.  Shapes are validated by the caller.
@@ -54,19 +54,20 @@ hipError_t launch_prep(const Shape &s, const void *q, const void *k, const void 
 // lb: log beta [BH][T][V] of the value-side gate, nullable (beta = 1)
 hipError_t launch_fwd_main(const Shape &s, const void *v, const void *lb, const float *S0, void *o, float *ST,
                            const Work &w, hipStream_t st);
-// gb_on: the general form (v, dO are then w.Vh, w.Oh; the states decay by w.gb)
-// ng: no gate and no gate gradient wanted (la and the backward's dla NULL)
-// The dq sweep: w.dqr (dq_inter), w.dP, w.cST.
-hipError_t launch_bwd_dq(const Shape &s, const void *k, const void *la, const void *v,
-                         const float *S0, const void *dO, const float *dST,
-                         const Work &w, hipStream_t st, bool ng, bool gb_on = false);
-// The intra-chunk terms of the backward, after the dq sweep: dq, and w.dki,
-// w.dai, w.dat for the dk sweep (w.dki only with ng).
-hipError_t launch_bwd_intra(const Shape &s, const void *q, const void *k, const void *la, void *dq, const Work &w,
-                            hipStream_t st, bool ng);
-hipError_t launch_bwd_dk(const Shape &s, const void *q, const void *k, const void *la,
-                         const void *v, const void *dO, const float *dST, const void *dq,
-                         void *dk, void *dla, const Work &w, hipStream_t st, bool gb_on = false);
+// The key sweeps, side by side in one launch: w.dqr, w.tq, w.dP, w.cST (dq) and
+// w.dkr, w.tk (dk).
+// ng: no gate and no gate gradient wanted (la and the backward's dla NULL;
+// w.tq, w.tk are then not written)
+// gb_on: the general form (v, dO are then w.Vh, w.Oh; the states decay by
+// w.gb); w.cpart as well.
+hipError_t launch_key_sweeps(const Shape &s, const void *q, const void *k, const void *la, const void *v,
+                             const float *S0, const void *dO, const float *dST, const Work &w, hipStream_t st, bool ng,
+                             bool gb_on = false);
+// The in-chunk terms of the backward, after both key sweeps: dq, dk and (unless
+// NULL) dla.  s is the unsegmented shape, run as nseg segments per head by the
+// sweeps.  has_dST: w.cST holds the final-state term.
+hipError_t launch_bwd_intra(const Shape &s, int nseg, const void *q, const void *k, const void *la, bool has_dST,
+                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng);
 // lb: log beta of the general form (nullable)
 hipError_t launch_bwd_dv(const Shape &s, const void *dO, const void *lb, const float *dST, void *dv, float *dS0,
                          const Work &w, hipStream_t st);
@@ -75,7 +76,7 @@ hipError_t launch_beta_prep(const Shape &s, const void *v, const void *dO, const
                             hipStream_t st);
 hipError_t launch_beta_grad(const Shape &s, const void *o, const void *dO, const void *v, const void *dv,
                             void *dlb, const Work &w, hipStream_t st);
-size_t ks_state_bytes(const Shape &s);
+size_t ks_state_elems(const Shape &s);
 hipError_t launch_recurrent(const Shape &s, const void *q, const void *k, const void *v,
                             const void *la, const void *lb, const float *S0, void *o, float *ST, hipStream_t st);
 // T == 0 edge: S_T = S0 (or 0); dS0 = dS_T (or 0).
@@ -99,8 +100,7 @@ hipError_t launch_seg_bwd_scan(int BH, int nseg, int K, int V, const float *dec,
 size_t lds_prep(const Shape &s);
 size_t lds_fwd_main(const Shape &s);
 size_t lds_bwd_intra(const Shape &s);
-size_t lds_bwd_dq(const Shape &s);
-size_t lds_bwd_dk(const Shape &s);
+size_t lds_key_sweeps(const Shape &s);
 size_t lds_bwd_dv(const Shape &s);
 
 constexpr size_t kMaxLds = 160 * 1024;

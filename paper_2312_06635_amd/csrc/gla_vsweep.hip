@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
   float *sE = (float *)(smem + L::offE), *sScan = (float *)(smem + L::offScan);
 
   int bh, tile;
-  xcd_map(a.BH, a.ntiles, bh, tile);
+  xcd_map(blockIdx.x, a.BH, a.ntiles, bh, tile);
   const int w = wave_id(), l = lane_id(), g = l >> 4, j = l & 15;
   const int cg = w & 3, kh = w >> 2;
   const int K = a.K, V = a.V, C = a.C, N = a.N;
