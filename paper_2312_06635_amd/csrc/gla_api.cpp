@@ -10,6 +10,7 @@
 
 namespace {
 
+using gla::Segs;
 using gla::Shape;
 using gla::Work;
 
@@ -55,15 +56,15 @@ gla_status make_shape(const gla_problem *p, Shape &s, bool chunked = true) {
 bool lds_bad(size_t bytes) { return bytes == 0 || bytes > gla::kMaxLds; }
 
 gla_status check_lds(const Shape &s, bool bwd) {
-  if (lds_bad(gla::lds_prep(s)) || lds_bad(gla::lds_fwd_main(s))) return GLA_ERR_UNSUPPORTED;
-  if (bwd && (lds_bad(gla::lds_bwd_intra(s)) || lds_bad(gla::lds_key_sweeps(s)) || lds_bad(gla::lds_bwd_dv(s))))
+  if (lds_bad(gla::lds_prep(s)) || lds_bad(gla::lds_value_passes(s))) return GLA_ERR_UNSUPPORTED;
+  if (bwd && (lds_bad(gla::lds_bwd_intra(s)) || lds_bad(gla::lds_key_sweeps(s))))
     return GLA_ERR_UNSUPPORTED;
   return GLA_OK;
 }
 
 // Sequence segments: with few heads and long sequences, each head's
 // sequence is split into nseg segments of whole chunks (at least four each),
-// processed as separate heads and joined by the segment scans of
+// walked as separate sequences and joined by the segment scans of
 // gla_segment.hip (App. A.2's two-stage form).  nseg minimises a simple cost:
 // the chunks each sweep walks in sequence times the rounds of 256 workgroups
 // it needs (key sweeps weighted 2 against 1 for the value sweeps, which run
@@ -71,16 +72,19 @@ gla_status check_lds(const Shape &s, bool bwd) {
 // alone, so forward and backward agree.  The general form (value-side gate)
 // is not segmented.
 int choose_nseg(const Shape &s) {
-  if (s.T <= 0 || s.T % s.C != 0) return 1;
+  if (s.T <= 0) return 1;
   const int64_t KT = (s.K + 31) / 32, VT = (s.V + 63) / 64;
   auto rounds = [](int64_t wgs) { return (wgs + 255) / 256; };
   auto cost = [&](int n) {
-    const int64_t steps = s.N / n;
+    const int64_t steps = (s.N + n - 1) / n;
     return 4 * rounds((int64_t)s.BH * n * KT) * steps + (n > 1 ? 4 : 2) * rounds((int64_t)s.BH * n * VT) * steps;
   };
   int best = 1;
   int64_t best_cost = cost(1);
-  for (int n = 2; s.N % n == 0 && s.N / n >= 4 && (int64_t)s.BH * n <= 65535; n *= 2) {
+  // (a count that does not divide the chunks leaves the last segment shorter;
+  // every segment keeps at least one chunk: (n - 1) ceil(N / n) < N)
+  for (int n = 2; s.N / n >= 4 && (int64_t)s.BH * n <= 65535; n *= 2) {
+    if ((int64_t)(n - 1) * ((s.N + n - 1) / n) >= s.N) continue;
     const int64_t c = cost(n);
     if (c < best_cost) {
       best = n;
@@ -101,17 +105,11 @@ int resolve_nseg(const Shape &s, uint32_t flags, bool general) {
   return want;
 }
 
-Shape seg_shape(const Shape &s, int nseg) {
-  Shape t = s;
-  t.BH = s.BH * nseg;
-  t.T = s.T / nseg;
-  t.N = s.N / nseg;
-  return t;
-}
+Segs make_segs(const Shape &s, int nseg) { return Segs{nseg, (s.N + nseg - 1) / nseg}; }
 
-// Workspace layout of the (segmented) shape s; op 1 extends op 0, op 2 (the
-// general form's backward) extends op 1.  Returns the total byte count and, if
-// base is non-null, the region pointers.
+// Workspace layout of the shape s in nseg segments; op 1 extends op 0, op 2
+// (the general form's backward) extends op 1.  Returns the total byte count
+// and, if base is non-null, the region pointers.
 size_t layout(const Shape &s, int op, char *base, Work *w, int nseg) {
   const size_t es = s.esz();
   const size_t rows = (size_t)s.BH * s.T, chunks = (size_t)s.BH * s.N;
@@ -125,13 +123,12 @@ size_t layout(const Shape &s, int op, char *base, Work *w, int nseg) {
   void *Kt = take(rows * s.K * es);
   void *P = take(chunks * s.C * s.C * es);
   void *gam = take(chunks * s.K * sizeof(float));
-  const size_t states = (size_t)s.BH * s.K * s.V * sizeof(float);  // s.BH counts the segments
-  void *Sin = nullptr, *Sloc = nullptr, *dec = nullptr, *dSout = nullptr;
-  if (nseg > 1) {
-    Sin = take(states);
-    Sloc = take(states);
-    dec = take((size_t)s.BH * s.K * sizeof(float));
-  }
+  // the states at the inner segment boundaries (with whole chunks the sizes
+  // documented for GLA_SEGMENTS are kept: 2 and 1 states per segment)
+  const size_t state = (size_t)s.BH * s.K * s.V * sizeof(float);
+  const bool whole = s.T % s.C == 0;
+  void *Sseg = nullptr, *dSseg = nullptr;
+  if (nseg > 1) Sseg = take(state * (whole ? 2 * nseg : nseg - 1));
   void *dP = nullptr, *dqr = nullptr, *dkr = nullptr, *tq = nullptr, *tk = nullptr, *cST = nullptr, *carry = nullptr;
   void *Vh = nullptr, *Oh = nullptr, *gb = nullptr, *Sb = nullptr, *Db = nullptr, *cpart = nullptr;
   if (op >= 1) {
@@ -141,10 +138,10 @@ size_t layout(const Shape &s, int op, char *base, Work *w, int nseg) {
     tq = take(chunks * s.K * sizeof(float));
     tk = take(chunks * s.K * sizeof(float));
     carry = take(chunks * s.K * sizeof(float));
-    cST = take((size_t)s.BH * s.K * sizeof(float));
+    cST = take((size_t)s.BH * nseg * s.K * sizeof(float));
     // (scalar gates: the documented extra bytes stay part of the size)
     if (s.sgate) take(rows * ((s.K + 31) / 32) * sizeof(float));
-    if (nseg > 1) dSout = take(states);
+    if (nseg > 1) dSseg = take(state * (whole ? nseg : nseg - 1));
   }
   if (op == 2) {
     Vh = take(rows * s.V * es);
@@ -159,7 +156,7 @@ size_t layout(const Shape &s, int op, char *base, Work *w, int nseg) {
     w->dP = (float *)dP; w->dqr = (float *)dqr; w->dkr = (float *)dkr; w->tq = (float *)tq; w->tk = (float *)tk;
     w->cST = (float *)cST; w->carry = (float *)carry;
     w->Vh = Vh; w->Oh = Oh; w->gb = (float *)gb; w->Sb = Sb; w->Db = (float *)Db; w->cpart = (float *)cpart;
-    w->Sin = (float *)Sin; w->Sloc = (float *)Sloc; w->dec = (float *)dec; w->dSout = (float *)dSout;
+    w->Sseg = (float *)Sseg; w->dSseg = (float *)dSseg;
   }
   return off;
 }
@@ -196,7 +193,7 @@ GLA_EXPORT size_t gla_workspace_bytes(const gla_problem *prob, int op) {
   if (make_shape(prob, s) != GLA_OK || op < 0 || op > 2) return 0;
   const int nseg = resolve_nseg(s, prob->flags, op == 2);
   if (nseg == 0) return 0;
-  return layout(seg_shape(s, nseg), op, nullptr, nullptr, nseg);
+  return layout(s, op, nullptr, nullptr, nseg);
 }
 
 namespace {
@@ -215,29 +212,22 @@ gla_status chunk_fwd(const gla_problem *prob, const void *q, const void *k, cons
   if (any && (!q || !k || !v || !o)) return GLA_ERR_NULL;
   const int nseg = resolve_nseg(s, prob->flags, log_beta != nullptr);
   if (nseg == 0) return GLA_ERR_UNSUPPORTED;
-  const Shape s2 = seg_shape(s, nseg);
-  const size_t need = layout(s2, 0, nullptr, nullptr, nseg);
+  const Segs sg = make_segs(s, nseg);
+  const size_t need = layout(s, 0, nullptr, nullptr, nseg);
   if (any && (!workspace || workspace_bytes < need)) return GLA_ERR_WORKSPACE;
   hipStream_t hs = (hipStream_t)stream;
   if (s.BH == 0) return GLA_OK;
   if (s.T == 0)
     return hip_status(gla::launch_copy_state((int64_t)s.BH * s.K * s.V, S0, S_T, hs));
   Work w;
-  layout(s2, 0, (char *)workspace, &w, nseg);
+  layout(s, 0, (char *)workspace, &w, nseg);
   alias_ungated(w, log_alpha, q, k);
   hipError_t e = hipSuccess;
-  if (stage == 0 || stage == 1) e = gla::launch_prep(s2, q, k, log_alpha, w, hs);
-  if (e == hipSuccess && (stage == 0 || stage == 2)) {
-    if (nseg == 1) {
-      e = gla::launch_fwd_main(s, v, log_beta, S0, o, S_T, w, hs);
-    } else {
-      // local final states, the segment scan, then the outputs from each
-      // segment's true initial state
-      e = gla::launch_fwd_main(s2, v, nullptr, nullptr, o, w.Sloc, w, hs);
-      if (e == hipSuccess) e = gla::launch_seg_decay(s2, w.gam, w.dec, hs);
-      if (e == hipSuccess) e = gla::launch_seg_fwd_scan(s.BH, nseg, s.K, s.V, w.dec, S0, w.Sloc, w.Sin, S_T, hs);
-      if (e == hipSuccess) e = gla::launch_fwd_main(s2, v, nullptr, w.Sin, o, nullptr, w, hs);
-    }
+  if (stage == 0 || stage == 1) e = gla::launch_prep(s, q, k, log_alpha, w, hs);
+  if (stage == 0 || stage == 2) {
+    // the states at the inner segment boundaries, then the outputs
+    if (e == hipSuccess && nseg > 1) e = gla::launch_seg_states(s, sg, false, v, S0, w, hs);
+    if (e == hipSuccess) e = gla::launch_fwd_main(s, sg, v, log_beta, S0, o, S_T, w, hs);
   }
   return hip_status(e);
 }
@@ -294,8 +284,8 @@ GLA_EXPORT gla_status gla_chunk_bwd(const gla_problem *prob, const void *q, cons
   if (any && (!q || !k || !v || !dO || !dq || !dk || !dv)) return GLA_ERR_NULL;
   const int nseg = resolve_nseg(s, prob->flags, false);
   if (nseg == 0) return GLA_ERR_UNSUPPORTED;
-  const Shape s2 = seg_shape(s, nseg);
-  const size_t need = layout(s2, 1, nullptr, nullptr, nseg);
+  const Segs sg = make_segs(s, nseg);
+  const size_t need = layout(s, 1, nullptr, nullptr, nseg);
   if (any && (!workspace || workspace_bytes < need)) return GLA_ERR_WORKSPACE;
   hipStream_t hs = (hipStream_t)stream;
   if (s.BH == 0) return GLA_OK;
@@ -305,35 +295,21 @@ GLA_EXPORT gla_status gla_chunk_bwd(const gla_problem *prob, const void *q, cons
   // no gate and no gate gradient: the kernels' alpha = 1 variants
   const bool ng = !log_alpha && !dlog_alpha;
   Work w;
-  layout(s2, 1, (char *)workspace, &w, nseg);
+  layout(s, 1, (char *)workspace, &w, nseg);
   alias_ungated(w, log_alpha, q, k);
   hipError_t e = hipSuccess;
   if (run(1) && !(prob->flags & GLA_FLAG_REUSE_FWD_WORKSPACE)) {
-    e = gla::launch_prep(s2, q, k, log_alpha, w, hs);
-    if (nseg > 1) {
-      // each segment's initial state, as in the forward (dv serves as scratch
-      // for the outputs, which are not needed here)
-      if (e == hipSuccess) e = gla::launch_fwd_main(s2, v, nullptr, nullptr, dv, w.Sloc, w, hs);
-      if (e == hipSuccess) e = gla::launch_seg_decay(s2, w.gam, w.dec, hs);
-      if (e == hipSuccess) e = gla::launch_seg_fwd_scan(s.BH, nseg, s.K, s.V, w.dec, S0, w.Sloc, w.Sin, nullptr, hs);
-    }
+    e = gla::launch_prep(s, q, k, log_alpha, w, hs);
+    if (e == hipSuccess && nseg > 1) e = gla::launch_seg_states(s, sg, false, v, S0, w, hs);
   }
-  // per segment: initial state and final-state gradient (the head's own S0
-  // and dS_T when unsegmented)
-  const float *S0s = nseg > 1 ? w.Sin : S0, *dSTs = nseg > 1 ? w.dSout : dS_T;
-  if (e == hipSuccess && run(2)) {
-    if (nseg > 1) {
-      // local initial-state gradients from a zero final-state gradient, then
-      // the reverse segment scan (which also gives the head's dS0)
-      e = gla::launch_bwd_dv(s2, dO, nullptr, nullptr, dv, w.Sloc, w, hs);
-      if (e == hipSuccess)
-        e = gla::launch_seg_bwd_scan(s.BH, nseg, s.K, s.V, w.dec, dS_T, w.Sloc, w.dSout, dS0, hs);
-    }
-    if (e == hipSuccess) e = gla::launch_key_sweeps(s2, q, k, log_alpha, v, S0s, dO, dSTs, w, hs, ng);
+  if (run(2)) {
+    // the final-state gradients of the inner segments, then the sweeps
+    if (e == hipSuccess && nseg > 1) e = gla::launch_seg_states(s, sg, true, dO, dS_T, w, hs);
+    if (e == hipSuccess) e = gla::launch_key_sweeps(s, sg, q, k, log_alpha, v, S0, dO, dS_T, w, hs, ng);
   }
   if (e == hipSuccess && run(3))
-    e = gla::launch_bwd_intra(s, nseg, q, k, log_alpha, dSTs != nullptr, dq, dk, dlog_alpha, w, hs, ng);
-  if (e == hipSuccess && run(5)) e = gla::launch_bwd_dv(s2, dO, nullptr, dSTs, dv, nseg > 1 ? nullptr : dS0, w, hs);
+    e = gla::launch_bwd_intra(s, sg, q, k, log_alpha, dS_T || nseg > 1, dq, dk, dlog_alpha, w, hs, ng);
+  if (e == hipSuccess && run(5)) e = gla::launch_bwd_dv(s, sg, dO, nullptr, dS_T, dv, dS0, w, hs);
   return hip_status(e);
 }
 
@@ -354,6 +330,7 @@ GLA_EXPORT gla_status gla_chunk_bwd_general(const gla_problem *prob, const void 
   if (any && (!q || !k || !v || !log_beta || !dO || !dq || !dk || !dv)) return GLA_ERR_NULL;
   if (any && dlog_beta && !o) return GLA_ERR_NULL;
   if (resolve_nseg(s, prob->flags, true) != 1) return GLA_ERR_UNSUPPORTED;
+  const Segs one = make_segs(s, 1);
   const size_t need = layout(s, 2, nullptr, nullptr, 1);
   if (any && (!workspace || workspace_bytes < need)) return GLA_ERR_WORKSPACE;
   hipStream_t hs = (hipStream_t)stream;
@@ -368,10 +345,10 @@ GLA_EXPORT gla_status gla_chunk_bwd_general(const gla_problem *prob, const void 
   if (run(1) && !(prob->flags & GLA_FLAG_REUSE_FWD_WORKSPACE))
     e = gla::launch_prep(s, q, k, log_alpha, w, hs);
   if (e == hipSuccess && run(2)) e = gla::launch_beta_prep(s, v, dO, log_beta, w, hs);
-  if (e == hipSuccess && run(3)) e = gla::launch_key_sweeps(s, q, k, log_alpha, w.Vh, S0, w.Oh, dS_T, w, hs, false, true);
+  if (e == hipSuccess && run(3)) e = gla::launch_key_sweeps(s, one, q, k, log_alpha, w.Vh, S0, w.Oh, dS_T, w, hs, false, true);
   if (e == hipSuccess && run(4))
-    e = gla::launch_bwd_intra(s, 1, q, k, log_alpha, dS_T != nullptr, dq, dk, dlog_alpha, w, hs, false);
-  if (e == hipSuccess && run(6)) e = gla::launch_bwd_dv(s, dO, log_beta, dS_T, dv, dS0, w, hs);
+    e = gla::launch_bwd_intra(s, one, q, k, log_alpha, dS_T != nullptr, dq, dk, dlog_alpha, w, hs, false);
+  if (e == hipSuccess && run(6)) e = gla::launch_bwd_dv(s, one, dO, log_beta, dS_T, dv, dS0, w, hs);
   if (e == hipSuccess && run(7) && dlog_beta)
     e = gla::launch_beta_grad(s, o, dO, v, dv, dlog_beta, w, hs);
   return hip_status(e);

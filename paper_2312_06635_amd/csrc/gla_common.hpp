@@ -223,6 +223,79 @@ template <typename T, int ROWS, int COLS, int NT> struct TileLd {
   }
 };
 
+// A [ROWS x RB bytes] tile copied from global memory straight into LDS (16
+// bytes a lane) by NT threads.  An instruction fills 1 KB of LDS, lane l at 16
+// l; the 16-byte chunk c of row r is to land at chunk c ^ SW(r), so the swizzle
+// is applied to the column each lane fetches.  Straight copies take no
+// registers and no LDS store instructions.  The compiler would wait for such a
+// load before any later LDS read (it cannot tell buffers apart), hence the
+// inline assembly; the loads have no register results, and dma_wait() stands
+// between them and the barrier that publishes the tile.
+template <int ROWS, int RB, int NT, typename SW> struct TileDma {
+  static constexpr int VPR = RB / 16;                     // 16-byte chunks per row
+  static constexpr int NI = (ROWS * VPR + 63) / 64;       // 1 KB instructions in all
+  static constexpr int NW = NT / 64;
+  static constexpr int NV = (NI + NW - 1) / NW;           // per wave
+  static_assert(ROWS * VPR % 64 == 0, "whole instructions");
+  uint32_t off[NV];
+  static __device__ __forceinline__ int pos(int w, int i) { return (w * NV + i) * 64 + lane_id(); }
+  static __device__ __forceinline__ int chunk(int w, int i) {
+    const int p = pos(w, i);
+    return (p % VPR) ^ SW::swz(p / VPR);
+  }
+  // rows `stride` bytes apart; rows >= rvalid and bytes >= bvalid of a row read as zero
+  __device__ __forceinline__ void init(int w, int stride, int rvalid, int bvalid) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int row = pos(w, i) / VPR, b = chunk(w, i) * 16;
+      off[i] = row < rvalid && b < bvalid ? (uint32_t)(row * stride + b) : 0x80000000u;
+    }
+  }
+  // src: the tile's first byte, `bytes` of the tensor from there on; dst: LDS
+  // byte address; bvalid: as in init(), for tiles narrower than the last
+  __device__ __forceinline__ void load(const void *src, uint32_t bytes, uint32_t dst, int w, int bvalid = RB) const {
+    const uint64_t base = (uint64_t)src;
+    const u32x4 rs = u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, bytes, 0x00020000u};
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if (NI % NW != 0 && w * NV + i >= NI) break;  // (uniform)
+      uint32_t o = off[i];
+      if (bvalid < RB && chunk(w, i) * 16 >= bvalid) o = 0x80000000u;
+      const uint32_t m = __builtin_amdgcn_readfirstlane(dst + (uint32_t)(w * NV + i) * 1024u);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(m), "v"(o), "s"(rs) : "m0", "memory");
+    }
+  }
+};
+// Wait until at most N of this wave's vector memory operations are outstanding
+// (they complete in order): all but the N youngest have.
+template <int N = 0> __device__ __forceinline__ void dma_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N < 63 ? N : 63) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+}
+
+// Sequence segments: a head's N chunks are walked as nseg sequences of Ns
+// chunks (the last may be shorter) that the sweeps treat as heads of their own.
+struct SegMap {
+  int head, seg;   // head and segment of "head" i of nheads * nseg
+  int rows, N;     // its steps and chunks
+  int64_t row0;    // its first row in a [BH][T] tensor
+  int64_t chunk0;  // its first chunk in a [BH][N] array
+};
+__device__ __forceinline__ SegMap seg_map(int head, int seg, int T, int C, int N, int Ns) {
+  SegMap m;
+  m.head = head;
+  m.seg = seg;
+  const int c0 = seg * Ns;
+  m.N = min(Ns, N - c0);
+  m.rows = min(Ns * C, T - c0 * C);
+  m.row0 = (int64_t)head * T + (int64_t)c0 * C;
+  m.chunk0 = (int64_t)head * N + c0;
+  return m;
+}
+
 // XCD-aware block mapping: consecutive workgroup ids are dealt round-robin to
 // the 8 XCDs, so when the head count is a multiple of 8 the tiles of one head
 // are all given ids with the same residue mod 8 (one XCD, one L2), letting

@@ -731,20 +731,20 @@ size_t lds_bwd_intra(const Shape &s) {
   return s.C == 16 ? IntraLayout<16>::total : (s.C == 32 ? IntraLayout<32>::total : IntraLayout<64>::total);
 }
 
-hipError_t launch_bwd_intra(const Shape &s, int nseg, const void *q, const void *k, const void *la, bool has_dST,
+hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, bool has_dST,
                             void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng) {
   IntraArgs a{};
   a.q = q; a.k = k; a.la = la; a.dP = w.dP; a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk;
   a.cST = has_dST ? w.cST : nullptr;
   a.dq = dq; a.dk = dk; a.dla = dla;
   a.T = s.T; a.K = s.K; a.C = s.C; a.N = s.N;
-  a.nseg = nseg; a.Ns = s.N / nseg;
+  a.nseg = sg.n; a.Ns = sg.Ns;
   a.sg = s.sgate ? 1 : 0;
   a.inv_tau = s.inv_tau;
   if (!ng && dla && a.Ns > kCarryDirect) {
     // (per workgroup the direct sum reads up to Ns rows of both arrays: beyond
     // a few dozen that costs more than this pass over them)
-    hipLaunchKernelGGL(carry_scan_kernel, dim3((s.K + 63) / 64, s.BH * nseg), dim3(64), 0, st, a, w.carry);
+    hipLaunchKernelGGL(carry_scan_kernel, dim3((s.K + 63) / 64, s.BH * sg.n), dim3(64), 0, st, a, w.carry);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     a.carry = w.carry;

@@ -94,11 +94,13 @@ struct KsArgs {
   float *dqr, *dkr;  // [BH][T][K] fp32 dq_inter, dk_inter
   float *tq, *tk;    // [BH][N][K] fp32 per chunk sums of q (.) dq_inter, k (.) dk_inter (not NG)
   float *dP;         // [BH][N][C][C] fp32 (dO V^T) (.) M per chunk, stored transposed ([s][t])
-  float *cST;        // [BH][K] rowsum(S_T (.) dS_T) (nullable dST: not written)
+  float *cST;        // [BH][nseg][K] rowsum(S_T (.) dS_T) per segment (not written with one segment and no dST)
   const float *gbv;  // general form: [BH][N][V] chunk decays exp(E_last) of the value-side gate
   void *Sb;          // general form: chunk-end states S_[n+1] (io), accumulator-native layout (sb_index)
   float *Db;         // general form: dS_[n+1] (fp32), the same layout
-  int BH, T, K, V, C, N, KT;
+  const float *Sseg, *dSseg;  // [BH][nseg - 1][K][V] states at the inner segment boundaries, and their gradients
+  int BH, T, K, V, C, Nh, KT;  // Nh: chunks per head
+  int nseg, Ns;   // segments per head, chunks per segment
   int ndq;        // workgroups of the dq sweep; the launch's others run the dk sweep
   int sg;         // scalar gate: la is [BH][T], one value per step shared by every feature
   float inv_tau;  // gate epilogue (0: la holds log alpha)
@@ -163,6 +165,9 @@ __device__ __forceinline__ int acc_value(int e, int g) { return perm32(8 * (e >>
 // read is one XOR (or none) away from it.
 template <typename T> constexpr int row_bytes() { return kVS * (int)sizeof(T); }
 __device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+struct SlabSwz {
+  static __device__ __forceinline__ int swz(int row) { return gla::swz(row); }
+};
 
 // Lane base of a row fragment (rows r0 + j, columns c0 + 8g; for fp32 half h
 // holds columns + 4h).
@@ -326,47 +331,6 @@ __device__ __forceinline__ float half_wave_sum(float x) {
   return x + __shfl_xor(x, 16);
 }
 
-// A [CP x 128] slab tile copied from global memory straight into LDS (16 bytes a
-// lane), stored with the swizzle above.  An instruction fills 1 KB of LDS, lane
-// l at 16 l, so the swizzle is applied to the column each lane fetches.
-// Straight copies take no registers and no LDS store instructions.  The compiler would wait for such a load before any later LDS
-// read (it cannot tell the buffers apart), hence the inline assembly; the
-// loads have no register results, and dma_wait() stands between them and the
-// barrier that publishes the tile.
-template <typename T, int CP> struct SlabDma {
-  static constexpr int VPR = row_bytes<T>() / 16;  // 16-byte chunks per row
-  static constexpr int NV = CP * VPR / kKT;        // instructions per wave
-  uint32_t off[NV];
-  // position of instruction i's lane in the tile, in 16-byte chunks
-  static __device__ __forceinline__ int pos(int w, int i) { return (w * NV + i) * 64 + lane_id(); }
-  static __device__ __forceinline__ int chunk(int w, int i) {
-    const int p = pos(w, i);
-    return (p % VPR) ^ swz(p / VPR);
-  }
-  // row stride V elements; rows >= rvalid read as zero
-  __device__ __forceinline__ void init(int w, int V, int rvalid) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int row = pos(w, i) / VPR;
-      off[i] = row < rvalid ? (uint32_t)(row * V * (int)sizeof(T) + chunk(w, i) * 16) : 0x80000000u;
-    }
-  }
-  // columns >= cvalid read as zero; dst: LDS byte address of the tile
-  __device__ __forceinline__ void load(const T *src, uint32_t bytes, int cvalid, uint32_t dst, int w) const {
-    const uint64_t base = (uint64_t)src;
-    const u32x4 rs = u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, bytes, 0x00020000u};
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      uint32_t o = off[i];
-      if (cvalid < kVS && chunk(w, i) * (16 / (int)sizeof(T)) >= cvalid) o = 0x80000000u;
-      const uint32_t m = __builtin_amdgcn_readfirstlane(dst + (uint32_t)(w * NV + i) * 1024u);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   :: "s"(m), "v"(o), "s"(rs) : "m0", "memory");
-    }
-  }
-};
-__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // RPT consecutive elements as LDS vector stores.
 template <typename T, int N> __device__ __forceinline__ void store_rows(T *p, const T (&v)[N]) {
 #pragma unroll
@@ -392,10 +356,11 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   float *sTot = (float *)(smem + L::offTot), *sOr = (float *)(smem + L::offOr);
 
   int bh, kt;
-  xcd_map(wg, a.BH, a.KT, bh, kt);
+  xcd_map(wg, a.BH * a.nseg, a.KT, bh, kt);
+  const SegMap sm = seg_map(bh / a.nseg, bh % a.nseg, a.T, a.C, a.Nh, a.Ns);
   const int tid = threadIdx.x, w = wave_id() & 3, l = lane_id();
   const int g = l >> 5, j = l & 31;  // 32x32 tile lane coordinates
-  const int K = a.K, V = a.V, C = a.C, N = a.N, k0 = kt * kKF;
+  const int K = a.K, V = a.V, C = a.C, N = sm.N, k0 = kt * kKF;
   const int fk = tid & 31, rg = tid >> 5, kf = k0 + fk;
   const bool fv = kf < K;
   constexpr int esz = sizeof(T);
@@ -405,8 +370,15 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   // ---- state, in groups of four consecutive values per lane (d_v is a
   // multiple of 16, so a group is inside or outside d_v as a whole; an absent
   // state, values past d_v and features past d_k read zero)
+  // the segment's initial state and final-state gradient: the head's at its
+  // ends, the segment scans' in between
+  const int64_t KV = (int64_t)K * V;
+  const float *segs = a.Sseg + ((int64_t)sm.head * (a.nseg - 1) + sm.seg) * KV;
+  const float *dsegs = a.dSseg + ((int64_t)sm.head * (a.nseg - 1) + sm.seg) * KV;
+  const float *S0 = sm.seg > 0 ? segs - KV : (a.S0 ? a.S0 + sm.head * KV : nullptr);
+  const float *dST = sm.seg < a.nseg - 1 ? dsegs : (a.dST ? a.dST + sm.head * KV : nullptr);
   auto load_state4 = [&](const float *src, int sl, int b) -> f4 {
-    const auto rs = make_rsrc(src ? src + (int64_t)bh * K * V : (const float *)a.v, src ? (uint32_t)(K * V * 4) : 0u);
+    const auto rs = make_rsrc(src ? src : (const float *)a.v, src ? (uint32_t)(K * V * 4) : 0u);
     const int vv = sl * kVS + 32 * w + acc_value(4 * b, g), kq = k0 + j;
     return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
                                       rs, vv < V && kq < K ? (uint32_t)((kq * V + vv) * 4) : 0x80000000u, 0, 0));
@@ -416,7 +388,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   for (int sl = 0; sl < NSL; ++sl) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const f4 x = load_state4(REV ? a.dST : a.S0, sl, b);
+      const f4 x = load_state4(REV ? dST : S0, sl, b);
 #pragma unroll
       for (int r = 0; r < 4; ++r) S[sl][4 * b + r] = x[r];
     }
@@ -425,7 +397,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
 
   // ---- input streams
   const int lrow = a.sg ? 1 : K;  // gate elements per step
-  const int64_t row0 = (int64_t)bh * a.T, chunk0 = (int64_t)bh * N;
+  const int64_t row0 = sm.row0, chunk0 = sm.chunk0;
   const T *gh = (const T *)(REV ? a.q : a.k) + row0 * K, *oh = (const T *)(REV ? a.k : a.q) + row0 * K;
   const T *lah = (const T *)a.la + row0 * lrow;
   const T *xh = (const T *)(REV ? a.v : a.dO) + row0 * V, *zh = (const T *)(REV ? a.dO : a.v) + row0 * V;
@@ -439,9 +411,9 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   float gbr[4];  // general form: the chunk's gb row (value v held by thread v mod 256)
   auto fetch_factors = [&](int n) {
     const int t0 = n * C;
-    const uint32_t bytes = rsrc_bytes((int64_t)(a.T - t0) * K * esz);
+    const uint32_t bytes = rsrc_bytes((int64_t)(sm.rows - t0) * K * esz);
     // an absent gate (alpha = 1) reads as log alpha = 0 from an empty range
-    const auto rs_la = make_rsrc(a.la ? lah + (int64_t)t0 * lrow : gh, a.la ? rsrc_bytes((int64_t)(a.T - t0) * lrow * esz) : 0u);
+    const auto rs_la = make_rsrc(a.la ? lah + (int64_t)t0 * lrow : gh, a.la ? rsrc_bytes((int64_t)(sm.rows - t0) * lrow * esz) : 0u);
     const auto rs_g = make_rsrc(gh + (int64_t)t0 * K, bytes), rs_o = make_rsrc(oh + (int64_t)t0 * K, bytes);
     // (the row offsets are formed anew for each chunk: kept across the loop
     // they would take RPT registers per tensor)
@@ -462,19 +434,19 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         gbr[i] = __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)((tid + kKT * i) * 4), 0, 0));
     }
   };
-  SlabDma<T, CP> dma;
-  dma.init(w, V, C);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+  TileDma<CP, row_bytes<T>(), kKT, SlabSwz> dma;
+  dma.init(w, V * esz, C, row_bytes<T>());
+  const uint32_t lds0 = lds_address(smem);
   const int NQ = N * NSL;
   auto chunk_of = [&](int it) { return REV ? N - 1 - it : it; };
   // slab q into its buffer (past the last slab: the last one again)
   auto fetch_slab = [&](int q) {
     const int qc = min(q, NQ - 1);
     const int it = qc / NSL, sl = qc - it * NSL, t0 = chunk_of(it) * C, c0 = sl * kVS;
-    const uint32_t bytes = rsrc_bytes(((int64_t)(a.T - t0) * V - c0) * esz);
+    const uint32_t bytes = rsrc_bytes(((int64_t)(sm.rows - t0) * V - c0) * esz);
     const uint32_t dst = lds0 + ((q & 1) ? 2 * (uint32_t)L::slab : 0u);
-    dma.load(xh + (int64_t)t0 * V + c0, bytes, V - c0, dst, w);
-    dma.load(zh + (int64_t)t0 * V + c0, bytes, V - c0, dst + (uint32_t)L::slab, w);
+    dma.load(xh + (int64_t)t0 * V + c0, bytes, dst, w, (V - c0) * esz);
+    dma.load(zh + (int64_t)t0 * V + c0, bytes, dst + (uint32_t)L::slab, w, (V - c0) * esz);
   };
 
   // ---- gate factors of a chunk, in two parts around a barrier (the row-group
@@ -486,7 +458,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   float al[RPT], scale[RPT], oth[RPT];
   auto factors_part1 = [&](int n) {
     if constexpr (!NG) {
-      const int rv = min(C, a.T - n * C);
+      const int rv = min(C, sm.rows - n * C);
       float s = 0.f;
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
@@ -678,7 +650,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     // (rows past the sequence end, past the chunk or of absent features fall
     // outside the buffer range and are dropped)
     {
-      const auto rs = make_rsrc(outh + (int64_t)t0 * K, rsrc_bytes((int64_t)(a.T - t0) * K * 4));
+      const auto rs = make_rsrc(outh + (int64_t)t0 * K, rsrc_bytes((int64_t)(sm.rows - t0) * K * 4));
       float tot = 0.f;
       uint32_t oo = ooff;
       asm volatile("" : "+v"(oo));
@@ -714,14 +686,14 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
 
   // ---- final-state term of the gate gradient: rowsum(S_T (.) dS_T) per feature
   if constexpr (!REV && !NG) {
-    if (a.dST) {
+    if (a.dST || a.nseg > 1) {  // (zero for a last segment without dS_T)
       float part = 0.f;
 #pragma unroll
       for (int sl = 0; sl < NSL; ++sl) {
         __builtin_amdgcn_sched_barrier(0);  // (one slab's loads at a time)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          const f4 x = load_state4(a.dST, sl, b);
+          const f4 x = load_state4(dST, sl, b);
 #pragma unroll
           for (int r = 0; r < 4; ++r) part += S[sl][4 * b + r] * x[r];
         }
@@ -751,7 +723,7 @@ __global__ void __launch_bounds__(kKT, (ks_waves<T, NSL>())) key_sweeps_kernel(K
 template <typename T> __global__ void __launch_bounds__(256) state_colsum_kernel(KsArgs a, int NSL, float *csum) {
   const int64_t id = (int64_t)blockIdx.x * 4 + wave_id();  // (bh, n, slab, wave)
   const int per = NSL * kNW;
-  if (id >= (int64_t)a.BH * a.N * per) return;
+  if (id >= (int64_t)a.BH * a.Nh * per) return;
   const int64_t cn = id / per;
   const int sw = (int)(id - cn * per), l = lane_id(), g = l >> 5, j = l & 31;
   const int v0 = (sw / kNW) * kVS + 32 * (sw % kNW);
@@ -830,18 +802,19 @@ size_t ks_state_elems(const Shape &s) {
   return (size_t)s.BH * s.N * kt * ks_nsl(s) * kVS * kKF;
 }
 
-hipError_t launch_key_sweeps(const Shape &s, const void *q, const void *k, const void *la, const void *v,
+hipError_t launch_key_sweeps(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, const void *v,
                              const float *S0, const void *dO, const float *dST, const Work &w, hipStream_t st, bool ng,
                              bool gb_on) {
   KsArgs a{};
   a.q = q; a.k = k; a.la = la; a.v = v; a.dO = dO; a.S0 = S0; a.dST = dST;
   a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk; a.dP = w.dP; a.cST = w.cST;
   if (gb_on) { a.gbv = w.gb; a.Sb = w.Sb; a.Db = w.Db; }
-  a.BH = s.BH; a.T = s.T; a.K = s.K; a.V = s.V; a.C = s.C; a.N = s.N;
+  a.BH = s.BH; a.T = s.T; a.K = s.K; a.V = s.V; a.C = s.C; a.Nh = s.N;
+  a.nseg = sg.n; a.Ns = sg.Ns; a.Sseg = w.Sseg; a.dSseg = w.dSseg;
   a.KT = (s.K + kKF - 1) / kKF;
   a.sg = s.sgate ? 1 : 0;
   a.inv_tau = s.inv_tau;
-  a.ndq = s.BH * a.KT;
+  a.ndq = s.BH * sg.n * a.KT;
   const int wgs = 2 * a.ndq;
   hipError_t e;
   if (s.io == IO_BF16)

@@ -6,6 +6,8 @@
 
 namespace gla {
 
+constexpr size_t kMaxLds = 160 * 1024;
+
 enum Io { IO_F32 = 0, IO_BF16 = 1 };
 
 // One validated problem.  N = number of chunks (the last may be shorter).
@@ -16,6 +18,12 @@ struct Shape {
   bool sgate;     // scalar gate: one gate value per (head, step), [BH][T]
   int esz() const { return io == IO_BF16 ? 2 : 4; }
   int la_row() const { return sgate ? 1 : K; }  // gate elements per step
+};
+
+// Sequence segments per head (1: the whole sequence) and their length in
+// chunks (the last segment may be shorter).
+struct Segs {
+  int n, Ns;
 };
 
 // Device workspace regions (see gla_api.cpp for the layout).
@@ -37,12 +45,9 @@ struct Work {
   void *Vh = nullptr;         // [BH][T][V] io : V (.) exp(-E)
   void *Oh = nullptr;         // [BH][T][V] io : dO (.) exp(E)
   float *gb = nullptr;        // [BH][N][V] fp32 : chunk decay exp(E_last)
-  // sequence segments (few heads, long sequences; the kernels then run on the
-  // segmented shape, whose heads are the segments)
-  float *Sin = nullptr;       // [BH nseg][K][V] fp32 : each segment's initial state
-  float *Sloc = nullptr;      // [BH nseg][K][V] fp32 : local final states; then local dS0
-  float *dec = nullptr;       // [BH nseg][K] fp32 : each segment's decay
-  float *dSout = nullptr;     // [BH nseg][K][V] fp32 : each segment's final-state gradient
+  // sequence segments (few heads, long sequences): the states between them
+  float *Sseg = nullptr;      // [BH][nseg - 1][K][V] fp32 : initial state of segment s + 1
+  float *dSseg = nullptr;     // [BH][nseg - 1][K][V] fp32 : final-state gradient of segment s
   void *Sb = nullptr;         // chunk-end states S_[n+1] (io), written by the dq sweep (ks_state_elems)
   float *Db = nullptr;        // their gradients dS_[n+1] (fp32), written by the dk sweep
   float *cpart = nullptr;     // [BH][N][V] fp32 : colsum(S_[n+1] (.) dS_[n+1])
@@ -51,26 +56,30 @@ struct Work {
 // Returns hipSuccess or the launch error.  Shapes are validated by the caller.
 hipError_t launch_prep(const Shape &s, const void *q, const void *k, const void *la,
                        const Work &w, hipStream_t st);
-// lb: log beta [BH][T][V] of the value-side gate, nullable (beta = 1)
-hipError_t launch_fwd_main(const Shape &s, const void *v, const void *lb, const float *S0, void *o, float *ST,
-                           const Work &w, hipStream_t st);
+// The forward state pass: o and S_T.  lb: log beta [BH][T][V] of the value-side
+// gate, nullable (beta = 1).
+hipError_t launch_fwd_main(const Shape &s, const Segs &sg, const void *v, const void *lb, const float *S0, void *o,
+                           float *ST, const Work &w, hipStream_t st);
+// The states at the inner segment boundaries: w.Sseg from the forward's inputs,
+// w.dSseg (rev) from the backward's.
+hipError_t launch_seg_states(const Shape &s, const Segs &sg, bool rev, const void *z, const float *R0, const Work &w,
+                             hipStream_t st);
 // The key sweeps, side by side in one launch: w.dqr, w.tq, w.dP, w.cST (dq) and
 // w.dkr, w.tk (dk).
 // ng: no gate and no gate gradient wanted (la and the backward's dla NULL;
 // w.tq, w.tk are then not written)
 // gb_on: the general form (v, dO are then w.Vh, w.Oh; the states decay by
 // w.gb); w.cpart as well.
-hipError_t launch_key_sweeps(const Shape &s, const void *q, const void *k, const void *la, const void *v,
+hipError_t launch_key_sweeps(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, const void *v,
                              const float *S0, const void *dO, const float *dST, const Work &w, hipStream_t st, bool ng,
                              bool gb_on = false);
 // The in-chunk terms of the backward, after both key sweeps: dq, dk and (unless
-// NULL) dla.  s is the unsegmented shape, run as nseg segments per head by the
-// sweeps.  has_dST: w.cST holds the final-state term.
-hipError_t launch_bwd_intra(const Shape &s, int nseg, const void *q, const void *k, const void *la, bool has_dST,
+// NULL) dla.  has_dST: w.cST holds the final-state terms.
+hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, bool has_dST,
                             void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng);
 // lb: log beta of the general form (nullable)
-hipError_t launch_bwd_dv(const Shape &s, const void *dO, const void *lb, const float *dST, void *dv, float *dS0,
-                         const Work &w, hipStream_t st);
+hipError_t launch_bwd_dv(const Shape &s, const Segs &sg, const void *dO, const void *lb, const float *dST, void *dv,
+                         float *dS0, const Work &w, hipStream_t st);
 // General form, value side: Vh, Oh, gb into w; then (after the sweeps) dlog beta.
 hipError_t launch_beta_prep(const Shape &s, const void *v, const void *dO, const void *lb, const Work &w,
                             hipStream_t st);
@@ -90,19 +99,17 @@ hipError_t launch_outgate_bwd(int B, int H, int T, int V, int io, const void *o,
                               const float *b, float eps, const void *dy, void *d_o, void *dg, float *dw,
                               float *db, float *part, hipStream_t st);
 
-// Sequence segments (gla_segment.hip); s2 is the segmented shape.
-hipError_t launch_seg_decay(const Shape &s2, const float *gam, float *dec, hipStream_t st);
-hipError_t launch_seg_fwd_scan(int BH, int nseg, int K, int V, const float *dec, const float *S0, const float *Sloc,
-                               float *Sin, float *ST, hipStream_t st);
-hipError_t launch_seg_bwd_scan(int BH, int nseg, int K, int V, const float *dec, const float *dST,
-                               const float *dS0loc, float *dSout, float *dS0, hipStream_t st);
+// The state-only pass for bf16 (gla_segstate.hip): w.Sseg, w.dSseg (rev) of each
+// segment from a zero state (the first in walking order: from R0).
+hipError_t launch_seg_pass(const Shape &s, const Segs &sg, bool rev, const void *z, const float *R0, const Work &w,
+                           hipStream_t st);
+// In place, from the states each segment adds to the true ones (gla_segment.hip).
+hipError_t launch_seg_scan(const Shape &s, const Segs &sg, bool rev, const float *gam, float *states, hipStream_t st);
 // LDS bytes each kernel needs (0 means the shape is not supported).
 size_t lds_prep(const Shape &s);
-size_t lds_fwd_main(const Shape &s);
+size_t lds_value_passes(const Shape &s);
 size_t lds_bwd_intra(const Shape &s);
 size_t lds_key_sweeps(const Shape &s);
-size_t lds_bwd_dv(const Shape &s);
 
-constexpr size_t kMaxLds = 160 * 1024;
 
 }  // namespace gla

@@ -1,14 +1,17 @@
 // gla_segment.hip -- sequence parallelism for few heads and long sequences
 // (the two-stage scan of App. A.2 over segments of whole chunks).  A head's
-// sequence [T] is viewed as nseg segments of T/nseg steps, which the kernels
-// treat as independent heads; these kernels connect them.  With D_s the decay
-// of segment s (the product of its chunk decays gamma, per key feature):
-//   forward:  S_in[0] = S0,  S_in[s+1] = Diag(D_s) S_in[s] + S_loc[s]
+// sequence is walked as nseg segments that the sweeps treat as independent
+// sequences.  With D_s the decay of segment s (the product of its chunk decays
+// gamma, per key feature), the states at the inner boundaries are
+//   forward:  S_in[s+1] = Diag(D_s) S_in[s] + S_loc[s],   s = 0 .. nseg - 2
 //             (S_loc[s]: segment s's final state from a zero initial state;
-//             S_in[nseg] is the head's S_T);
-//   backward: dS_out[nseg-1] = dS_T,  dS_out[s-1] = Diag(D_s) dS_out[s] + dS0_loc[s]
+//             for s = 0 from S0, i.e. already S_in[1]);
+//   backward: dS_out[s-1] = Diag(D_s) dS_out[s] + dS0_loc[s],   s = nseg - 1 .. 1
 //             (dS0_loc[s]: the gradient of segment s's initial state from a
-//             zero final-state gradient; the head's dS0 continues one more step).
+//             zero final-state gradient; for the last s from dS_T).
+// The state-only passes leave S_loc[s] in entry s and dS0_loc[s] in entry s - 1
+// of [BH][nseg - 1][K][V]; the scan turns them into S_in[s + 1] and dS_out[s -
+// 1] in place.  The whole sequence's S_T and dS0 come from the full passes.
 #include "gla_common.hpp"
 #include "gla_launch.hpp"
 
@@ -16,77 +19,66 @@ namespace gla {
 
 namespace {
 
-// dec[seg][k] = product of the segment's chunk decays.
-__global__ void __launch_bounds__(256) seg_decay_kernel(const float *gam, float *dec, int64_t n, int Ns, int K) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int64_t seg = i / K;
-  const int k = (int)(i - seg * K);
-  const float *g = gam + seg * Ns * K + k;
-  float d = 1.f;
-  for (int c = 0; c < Ns; ++c) d *= g[(int64_t)c * K];
-  dec[i] = d;
-}
+struct ScanArgs {
+  const float *gam;  // [BH][N][K] chunk decays
+  float *X;          // [BH][nseg - 1][K][V]
+  int N, Ns, K, V, ne;  // ne = nseg - 1
+};
 
-// Thread per (head, key feature, value column) element of the state.
-__global__ void __launch_bounds__(256) seg_fwd_scan_kernel(const float *dec, const float *S0, const float *Sloc,
-                                                           float *Sin, float *ST, int64_t n, int nseg, int K,
-                                                           int V) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int64_t KV = (int64_t)K * V, bh = i / KV, e = i - bh * KV;
-  const int k = (int)(e / V);
-  float S = S0 ? S0[i] : 0.f;
-  for (int s = 0; s < nseg; ++s) {
-    const int64_t seg = bh * nseg + s;
-    Sin[seg * KV + e] = S;
-    S = dec[seg * K + k] * S + Sloc[seg * KV + e];
+// A workgroup owns kRows key features of one head: their segment decays go to
+// LDS first (a product per thread, its chunks' loads independent), then a
+// thread walks the entries of four value columns.
+constexpr int kRows = 4;
+constexpr int kMaxSeg = 64;  // entries whose decays are held at a time
+
+template <bool REV> __global__ void __launch_bounds__(256) seg_scan_kernel(ScanArgs a) {
+  __shared__ float sD[kMaxSeg][kRows];
+  const int k0 = blockIdx.x * kRows, bh = blockIdx.y;
+  const int64_t KV = (int64_t)a.K * a.V;
+  float *Xh = a.X + (int64_t)bh * a.ne * KV;
+  const int V4 = a.V / 4, per = kRows * V4;  // (K is a multiple of 16)
+  for (int e0 = 1; e0 < a.ne; e0 += kMaxSeg) {
+    // entry e takes D_seg times the entry before it: seg = e forward, ne - e in reverse
+    const int cnt = min(kMaxSeg, a.ne - e0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cnt * kRows; i += 256) {
+      const int e = e0 + i / kRows, k = k0 + i % kRows, seg = REV ? a.ne - e : e;
+      const float *g = a.gam + ((int64_t)bh * a.N + (int64_t)seg * a.Ns) * a.K + k;
+      const int nc = min(a.Ns, a.N - seg * a.Ns);
+      float d = 1.f;
+      for (int c = 0; c < nc; c += 8) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = g[(int64_t)min(c + u, nc - 1) * a.K];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) d *= c + u < nc ? x[u] : 1.f;
+      }
+      sD[i / kRows][i % kRows] = d;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < per; i += 256) {
+      const int kr = i / V4;
+      const int64_t at = (int64_t)(k0 + kr) * a.V + 4 * (i - kr * V4);
+      auto entry = [&](int e) { return (f4 *)(Xh + (int64_t)(REV ? a.ne - 1 - e : e) * KV + at); };
+      f4 s = *entry(e0 - 1), x = *entry(e0);
+      for (int c = 0; c < cnt; ++c) {
+        const f4 nx = *entry(min(e0 + c + 1, a.ne - 1));  // (one entry ahead)
+        s = s * sD[c][kr] + x;
+        *entry(e0 + c) = s;
+        x = nx;
+      }
+    }
   }
-  if (ST) ST[i] = S;
 }
-
-__global__ void __launch_bounds__(256) seg_bwd_scan_kernel(const float *dec, const float *dST, const float *dS0loc,
-                                                           float *dSout, float *dS0, int64_t n, int nseg, int K,
-                                                           int V) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int64_t KV = (int64_t)K * V, bh = i / KV, e = i - bh * KV;
-  const int k = (int)(e / V);
-  float D = dST ? dST[i] : 0.f;
-  for (int s = nseg - 1; s >= 0; --s) {
-    const int64_t seg = bh * nseg + s;
-    dSout[seg * KV + e] = D;
-    D = dec[seg * K + k] * D + dS0loc[seg * KV + e];
-  }
-  if (dS0) dS0[i] = D;
-}
-
-unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-hipError_t launch_seg_decay(const Shape &s2, const float *gam, float *dec, hipStream_t st) {
-  const int64_t n = (int64_t)s2.BH * s2.K;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(seg_decay_kernel, dim3(blocks_of(n)), dim3(256), 0, st, gam, dec, n, s2.N, s2.K);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_fwd_scan(int BH, int nseg, int K, int V, const float *dec, const float *S0, const float *Sloc,
-                               float *Sin, float *ST, hipStream_t st) {
-  const int64_t n = (int64_t)BH * K * V;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(seg_fwd_scan_kernel, dim3(blocks_of(n)), dim3(256), 0, st, dec, S0, Sloc, Sin, ST, n, nseg, K,
-                     V);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_bwd_scan(int BH, int nseg, int K, int V, const float *dec, const float *dST,
-                               const float *dS0loc, float *dSout, float *dS0, hipStream_t st) {
-  const int64_t n = (int64_t)BH * K * V;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(seg_bwd_scan_kernel, dim3(blocks_of(n)), dim3(256), 0, st, dec, dST, dS0loc, dSout, dS0, n,
-                     nseg, K, V);
+hipError_t launch_seg_scan(const Shape &s, const Segs &sg, bool rev, const float *gam, float *states, hipStream_t st) {
+  if (sg.n <= 2) return hipSuccess;  // (the one boundary's state is the pass's own)
+  const ScanArgs a{gam, states, s.N, sg.Ns, s.K, s.V, sg.n - 1};
+  const dim3 grid(s.K / kRows, s.BH);
+  if (rev) hipLaunchKernelGGL(seg_scan_kernel<true>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(seg_scan_kernel<false>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

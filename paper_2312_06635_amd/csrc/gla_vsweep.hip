@@ -69,7 +69,10 @@ struct SweepArgs {
   const void *LB;   // log beta [BH][T][V] (value-side gate; the GB variant only)
   void *out;
   float *RN;        // final state (nullable)
+  float *Rseg;      // [BH][nseg - 1][K][V] states at the inner segment boundaries
   int BH, T, K, V, C, N, ntiles;
+  int nseg, Ns;     // segments per head, chunks per segment
+  int states_only;  // 1: no output, the boundary states into Rseg (fp32)
 };
 
 template <typename T> struct Pads;
@@ -177,11 +180,22 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
   T *sLB = (T *)(smem + L::offLB);
   float *sE = (float *)(smem + L::offE), *sScan = (float *)(smem + L::offScan);
 
-  int bh, tile;
-  xcd_map(blockIdx.x, a.BH, a.ntiles, bh, tile);
+  const int nst = a.nseg - a.states_only;  // sequences per head of this launch
+  int id, tile;
+  xcd_map(blockIdx.x, a.BH * nst, a.ntiles, id, tile);
+  const SegMap sm = seg_map(id / nst, id % nst + (a.states_only && REV ? 1 : 0), a.T, a.C, a.N, a.Ns);
+  const bool wo = sizeof(T) == 2 || a.states_only == 0;  // output wanted
+  const int64_t KV = (int64_t)a.K * a.V;
+  // initial state: the sequence's own at its first segment, else the segment
+  // scan's (state only: zero)
+  const float *R0 = (REV ? sm.seg == a.nseg - 1 : sm.seg == 0) ? (a.R0 ? a.R0 + sm.head * KV : nullptr)
+                    : (wo ? a.Rseg + ((int64_t)sm.head * (a.nseg - 1) + (REV ? sm.seg : sm.seg - 1)) * KV : nullptr);
+  float *RN = nullptr;
+  if (!wo) RN = a.Rseg + ((int64_t)sm.head * (a.nseg - 1) + (REV ? sm.seg - 1 : sm.seg)) * KV;
+  else if (a.RN && (REV ? sm.seg == 0 : sm.seg == a.nseg - 1)) RN = a.RN + sm.head * KV;
   const int w = wave_id(), l = lane_id(), g = l >> 4, j = l & 15;
   const int cg = w & 3, kh = w >> 2;
-  const int K = a.K, V = a.V, C = a.C, N = a.N;
+  const int K = a.K, V = a.V, C = a.C, N = sm.N, steps = sm.rows;
   const int v0 = tile * kTile;
   const int cbase = 16 * cg;                // first column of this wave, tile-local
   const bool active = v0 + cbase < V;       // V is a multiple of 16
@@ -211,7 +225,7 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int f = fbase + 32 * (kb >> 1) + 8 * g + 4 * (kb & 1) + r;
-      R[kb][r] = (a.R0 && active && f < K) ? a.R0[((int64_t)bh * K + f) * V + col] : 0.f;
+      R[kb][r] = (R0 && active && f < K) ? R0[(int64_t)f * V + col] : 0.f;
     }
 
   // ---- tile loaders (per-lane offsets fixed for the sweep); two register
@@ -235,21 +249,21 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
   if constexpr (GB) st1.b = st0.z;
   const int esz = sizeof(T);
   const uint32_t goff = (int)threadIdx.x < K ? 4u * threadIdx.x : 0x80000000u;  // gamma: lanes past K read 0
-  const T *Xh = (const T *)a.X + (int64_t)bh * a.T * K;
-  const T *Yh = (const T *)a.Y + (int64_t)bh * a.T * K;
-  const T *Zh = (const T *)a.Z + (int64_t)bh * a.T * V + v0;
-  const T *LBh = GB ? (const T *)a.LB + (int64_t)bh * a.T * V + v0 : Zh;
-  const T *Ph = (const T *)a.P + (int64_t)bh * N * C * C;
-  const float *Gh = a.gam + (int64_t)bh * N * K;
+  const T *Xh = (const T *)a.X + sm.row0 * K;
+  const T *Yh = (const T *)a.Y + sm.row0 * K;
+  const T *Zh = (const T *)a.Z + sm.row0 * V + v0;
+  const T *LBh = GB ? (const T *)a.LB + sm.row0 * V + v0 : Zh;
+  const T *Ph = (const T *)a.P + sm.chunk0 * C * C;
+  const float *Gh = a.gam + sm.chunk0 * K;
   auto chunk_of = [&](int it) { return REV ? N - 1 - it : it; };
   // part 0: X tile, 1: Y tile, 2: value tile, 3: P tile and gamma
   auto fetch_part = [&](Stage &S, int n, int part) {
     const int t0 = n * C;
-    const uint32_t remK = rsrc_bytes((int64_t)(a.T - t0) * K * esz);
+    const uint32_t remK = rsrc_bytes((int64_t)(steps - t0) * K * esz);
     if (part == 0) S.x.load(make_rsrc(Xh + (int64_t)t0 * K, remK));
     if (part == 1) S.y.load(make_rsrc(Yh + (int64_t)t0 * K, remK));
     if (part == 2) {
-      const uint32_t remV = rsrc_bytes(((int64_t)(a.T - t0) * V - v0) * esz);
+      const uint32_t remV = rsrc_bytes(((int64_t)(steps - t0) * V - v0) * esz);
       S.z.load(make_rsrc(Zh + (int64_t)t0 * V, remV));
       if constexpr (GB) S.b.load(make_rsrc(LBh + (int64_t)t0 * V, remV));
     }
@@ -263,10 +277,10 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
     for (int part = 0; part < 4; ++part) fetch_part(S, n, part);
   };
 
-  T *outh = (T *)a.out + (int64_t)bh * a.T * V;
+  T *outh = (T *)a.out + sm.row0 * V;
   auto body = [&](Stage &S, int it) {
     const int n = chunk_of(it);
-    const int t0 = n * C, rv = min(C, a.T - t0);
+    const int t0 = n * C, rv = min(C, steps - t0);
     S.x.store(sX, L::LDX);
     if constexpr (XS) {
       S.y.store_xor8(sY, KP, [](int r) { return swz_key<KP>(r); });
@@ -325,14 +339,16 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
     for (int s = 0; s < NS; ++s) {
       const frag_t<T> ra = acc_frag<T>(R[2 * s], R[2 * s + 1]);
 #pragma unroll
-      for (int I = 0; I < NI; ++I) acc[I] = mma<T>(acc[I], ra, ld_row<T>(sX, L::LDX, 16 * I, fbase + 32 * s));
+      for (int I = 0; I < NI; ++I)
+        if (wo) acc[I] = mma<T>(acc[I], ra, ld_row<T>(sX, L::LDX, 16 * I, fbase + 32 * s));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int part = s * 4 / NS; part < (s + 1) * 4 / NS; ++part) fetch_part(S, nf, part);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (active) {
-      if (kh == 0) {
+      if (!wo) {
+      } else if (kh == 0) {
         // intra-chunk term: O += P V (forward) or dV += P^T dO (backward)
 #pragma unroll
         for (int I = 0; I < NI; ++I) {
@@ -381,7 +397,7 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
       }
     }
     __syncthreads();
-    if (active && kh == 0) {
+    if (wo && active && kh == 0) {
 #pragma unroll
       for (int I = 0; I < NI; ++I) {
         f4 o = acc[I] + sO[(cg * NI + I) * 64 + l];
@@ -409,13 +425,13 @@ __global__ void __launch_bounds__(kThreads) sweep_kernel(SweepArgs a) {
     body(st0, it);
     if (it + 1 < N) body(st1, it + 1);
   }
-  if (a.RN && active) {
+  if (RN && active) {
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int f = fbase + 32 * (kb >> 1) + 8 * g + 4 * (kb & 1) + r;
-        if (f < K) a.RN[((int64_t)bh * K + f) * V + col] = R[kb][r];
+        if (f < K) RN[(int64_t)f * V + col] = R[kb][r];
       }
   }
 }
@@ -446,7 +462,8 @@ hipError_t launch_sweep_gb(const SweepArgs &a, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute((const void *)sweep_kernel<T, KP, CP, REV, GB>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   (void)attr;
-  hipLaunchKernelGGL((sweep_kernel<T, KP, CP, REV, GB>), dim3(a.BH * a.ntiles), dim3(kThreads), lds, st, a);
+  const int wgs = a.BH * (a.nseg - a.states_only) * a.ntiles;
+  hipLaunchKernelGGL((sweep_kernel<T, KP, CP, REV, GB>), dim3(wgs), dim3(kThreads), lds, st, a);
   return hipGetLastError();
 }
 
@@ -469,30 +486,41 @@ hipError_t dispatch_sweep(const Shape &s, const SweepArgs &a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-SweepArgs sweep_args(const Shape &s) {
+}  // namespace
+
+size_t lds_value_passes(const Shape &s) { return sweep_lds(s); }
+
+namespace {
+hipError_t launch_vsweep(const Shape &s, const Segs &sg, bool rev, bool states_only, const void *z, const void *lb,
+                         const float *R0, void *out, float *RN, const Work &w, hipStream_t st) {
   SweepArgs a{};
   a.BH = s.BH; a.T = s.T; a.K = s.K; a.V = s.V; a.C = s.C; a.N = s.N;
   a.ntiles = (s.V + kTile - 1) / kTile;
-  return a;
+  a.nseg = sg.n; a.Ns = sg.Ns; a.states_only = states_only ? 1 : 0;
+  a.X = rev ? w.Kt : w.Qt;
+  a.Y = rev ? w.Qt : w.Kt;
+  a.Z = z; a.P = w.P; a.gam = w.gam; a.R0 = R0; a.Rseg = rev ? w.dSseg : w.Sseg; a.out = out; a.RN = RN; a.LB = lb;
+  if (s.io == IO_BF16) return rev ? dispatch_sweep<bf16, true>(s, a, st) : dispatch_sweep<bf16, false>(s, a, st);
+  return rev ? dispatch_sweep<float, true>(s, a, st) : dispatch_sweep<float, false>(s, a, st);
 }
 
 }  // namespace
 
-size_t lds_fwd_main(const Shape &s) { return sweep_lds(s); }
-size_t lds_bwd_dv(const Shape &s) { return sweep_lds(s); }
-
-hipError_t launch_fwd_main(const Shape &s, const void *v, const void *lb, const float *S0, void *o, float *ST,
-                           const Work &w, hipStream_t st) {
-  SweepArgs a = sweep_args(s);
-  a.X = w.Qt; a.Y = w.Kt; a.Z = v; a.P = w.P; a.gam = w.gam; a.R0 = S0; a.out = o; a.RN = ST; a.LB = lb;
-  return s.io == IO_BF16 ? dispatch_sweep<bf16, false>(s, a, st) : dispatch_sweep<float, false>(s, a, st);
+hipError_t launch_fwd_main(const Shape &s, const Segs &sg, const void *v, const void *lb, const float *S0, void *o,
+                           float *ST, const Work &w, hipStream_t st) {
+  return launch_vsweep(s, sg, false, false, v, lb, S0, o, ST, w, st);
 }
 
-hipError_t launch_bwd_dv(const Shape &s, const void *dO, const void *lb, const float *dST, void *dv, float *dS0,
-                         const Work &w, hipStream_t st) {
-  SweepArgs a = sweep_args(s);
-  a.X = w.Kt; a.Y = w.Qt; a.Z = dO; a.P = w.P; a.gam = w.gam; a.R0 = dST; a.out = dv; a.RN = dS0; a.LB = lb;
-  return s.io == IO_BF16 ? dispatch_sweep<bf16, true>(s, a, st) : dispatch_sweep<float, true>(s, a, st);
+hipError_t launch_bwd_dv(const Shape &s, const Segs &sg, const void *dO, const void *lb, const float *dST, void *dv,
+                         float *dS0, const Work &w, hipStream_t st) {
+  return launch_vsweep(s, sg, true, false, dO, lb, dST, dv, dS0, w, st);
+}
+
+hipError_t launch_seg_states(const Shape &s, const Segs &sg, bool rev, const void *z, const float *R0, const Work &w,
+                             hipStream_t st) {
+  const hipError_t e = s.io == IO_BF16 ? launch_seg_pass(s, sg, rev, z, R0, w, st)
+                                       : launch_vsweep(s, sg, rev, true, z, nullptr, R0, nullptr, nullptr, w, st);
+  return e != hipSuccess ? e : launch_seg_scan(s, sg, rev, w.gam, rev ? w.dSseg : w.Sseg, st);
 }
 
 }  // namespace gla
