@@ -51,18 +51,18 @@
  *     (tested with per-step log alpha down to -50).
  *   - There is no scale argument (Eq. 3 has none): pre-scale k if desired.
  *
- * Few heads, long sequences: when B*H is too small to fill the GPU and T is
- * a multiple of the chunk, the chunkwise calls split each head's sequence into
- * segments of whole chunks, run them as separate heads and join them with
- * segment scans over the chunk decays (the two-stage form of App. A.2).  This
- * is decided from the shape alone (so gla_workspace_bytes accounts for it and
- * a forward's workspace stays valid for the backward's reuse flag), changes
- * only the summation order, and keeps the stage selector's meaning (forward
- * stage 2 then holds both state passes and the scan; backward stage 1 also
- * rebuilds the segments' initial states, stage 2 also their final-state
- * gradients).  GLA_SEGMENTS(n) in the flags fixes the segment count instead,
- * up to one chunk per segment (materialized chunk states).  The general form
- * (value-side gate) is never segmented.
+ * Few heads, long sequences: when B*H is too small to fill the GPU, the
+ * chunkwise calls split each head's sequence into segments of whole chunks
+ * (the last may be shorter, and end with a shorter chunk), walk them as
+ * separate sequences and join them with segment scans over the chunk decays
+ * (the two-stage form of App. A.2).  This is decided from the shape alone (so
+ * gla_workspace_bytes accounts for it and a forward's workspace stays valid
+ * for the backward's reuse flag), changes only the summation order, and keeps
+ * the stage selector's meaning (forward stage 2 then holds both state passes
+ * and the scan; backward stage 1 also rebuilds the segments' initial states,
+ * stage 2 also their final-state gradients).  GLA_SEGMENTS(n) in the flags
+ * fixes the segment count instead, up to one chunk per segment (materialized
+ * chunk states).  The general form (value-side gate) is never segmented.
  *
  * Supported shapes: B*H <= 65535; d_k and d_v multiples of 16 with d_k <= 256
  * and d_v <= 1024 (fp32 io additionally needs d_k <= 128); chunk C in
@@ -202,7 +202,9 @@ gla_status gla_chunk_fwd(const gla_problem *prob, const void *q, const void *k, 
  * every GPU the library runs on holds from the library's load until the
  * process ends.  The caller still provides every input and output buffer.
  * Problems whose forward workspace (gla_workspace_bytes(prob, 0)) exceeds
- * that size return GLA_ERR_SCRATCH before anything is enqueued.  The call
+ * that size return GLA_ERR_SCRATCH before anything is enqueued (with a T that
+ * is no multiple of the chunk: whose unsegmented workspace does; segments that
+ * do not fit are then left out, which changes the summation order).  The call
  * allocates, frees and clears nothing; its first call on a device looks up
  * that device's address of the array (hipGetSymbolAddress).  Every call on
  * one GPU uses that GPU's one array, so calls whose work overlaps on a GPU

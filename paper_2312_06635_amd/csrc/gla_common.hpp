@@ -238,7 +238,13 @@ template <int ROWS, int RB, int NT, typename SW> struct TileDma {
   static constexpr int NV = (NI + NW - 1) / NW;           // per wave
   static_assert(ROWS * VPR % 64 == 0, "whole instructions");
   uint32_t off[NV];
-  static __device__ __forceinline__ int pos(int w, int i) { return (w * NV + i) * 64 + lane_id(); }
+  // (a tile of fewer instructions than waves: some are issued twice, so that
+  // every wave issues NV and its outstanding ones can be counted)
+  static __device__ __forceinline__ int instr(int w, int i) {
+    const int p = w * NV + i;
+    return NW * NV == NI ? p : p % NI;
+  }
+  static __device__ __forceinline__ int pos(int w, int i) { return instr(w, i) * 64 + lane_id(); }
   static __device__ __forceinline__ int chunk(int w, int i) {
     const int p = pos(w, i);
     return (p % VPR) ^ SW::swz(p / VPR);
@@ -258,10 +264,9 @@ template <int ROWS, int RB, int NT, typename SW> struct TileDma {
     const u32x4 rs = u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, bytes, 0x00020000u};
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      if (NI % NW != 0 && w * NV + i >= NI) break;  // (uniform)
       uint32_t o = off[i];
       if (bvalid < RB && chunk(w, i) * 16 >= bvalid) o = 0x80000000u;
-      const uint32_t m = __builtin_amdgcn_readfirstlane(dst + (uint32_t)(w * NV + i) * 1024u);
+      const uint32_t m = __builtin_amdgcn_readfirstlane(dst + (uint32_t)instr(w, i) * 1024u);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(m), "v"(o), "s"(rs) : "m0", "memory");
     }

@@ -54,9 +54,16 @@ GLA_EXPORT gla_status gla_chunk_fwd_noalloc(const gla_problem *prob, const void 
   // 0 bytes: an invalid problem (the forward's validation returns its error
   // before any HIP call) or one with nothing to compute
   if (need == 0) return gla_chunk_fwd(prob, q, k, v, log_alpha, S0, o, S_T, nullptr, 0, stream);
-  if (need > kScratchBytes) return GLA_ERR_SCRATCH;
+  gla_problem p = *prob;
+  if (need > kScratchBytes) {
+    // a sequence with a shorter last chunk whose segment states alone exceed
+    // the array runs unsegmented
+    if (p.T % p.chunk == 0 || (p.flags & GLA_SEGMENTS_MASK) != 0) return GLA_ERR_SCRATCH;
+    p.flags |= GLA_SEGMENTS(1);
+    if (gla_workspace_bytes(&p, 0) > kScratchBytes) return GLA_ERR_SCRATCH;
+  }
   void *ws = nullptr;
   const gla_status st = scratch_ptr(&ws);
   if (st != GLA_OK) return st;
-  return gla_chunk_fwd(prob, q, k, v, log_alpha, S0, o, S_T, ws, kScratchBytes, stream);
+  return gla_chunk_fwd(&p, q, k, v, log_alpha, S0, o, S_T, ws, kScratchBytes, stream);
 }

@@ -5,14 +5,15 @@
 // with Y = K (.) Gamma, Z = V over the chunks in order, or (reverse) Y = Q (.)
 // Lambda, Z = dO backwards.
 //
-// A workgroup of 4 waves owns 64 value columns of one segment; wave (fw, cw)
-// holds features [fw KP/2, (fw + 1) KP/2) x columns 32 cw .. +32 of R as 32x32
-// fp32 accumulators.  With no output to form, a chunk is one pass over its Y
+// A workgroup owns 64 value columns of one segment; wave (fw, cw) of its 2 FW
+// holds features [fw KP/FW, (fw + 1) KP/FW) x columns 32 cw .. +32 of R as 32x32
+// fp32 accumulators (FW = 4 where the width divides, so that two waves per
+// SIMD cover each other's LDS reads; else 2).  With no output to form, a chunk is one pass over its Y
 // and Z tiles, copied straight into LDS three deep and read with transpose
 // reads; gamma's row travels with them (loaded per lane it would take as much
-// of the load path as both tiles: 72 us against SEGUS on 4 heads x 16384 steps
-// in 8 segments, d_k 256, d_v 512).  Running the full pass for its states took
-// 92 us forward and 100 us in reverse there.
+// of the load path as both tiles).  On 4 heads x 16384 steps in 8 segments (d_k
+// 256, d_v 512) the pass takes 54 us, with 4 waves 74; running the full pass
+// for its states took 92 us forward and 100 us in reverse.
 #include "gla_common.hpp"
 #include "gla_launch.hpp"
 
@@ -20,7 +21,6 @@ namespace gla {
 
 namespace {
 
-constexpr int kTh = 256;    // threads
 constexpr int kCols = 64;   // value columns per workgroup
 constexpr int NB = 3;       // buffers
 
@@ -38,6 +38,7 @@ struct SegArgs {
 template <int KP, int CP> struct SegLayout {
   static constexpr int RBY = KP <= 64 ? 128 : (KP <= 128 ? 256 : 512);  // bytes of a key-tile row
   static constexpr int RBZ = 2 * kCols;
+  static constexpr int FW = KP % 128 == 0 ? 4 : 2, threads = 128 * FW;
   static constexpr size_t y = (size_t)CP * RBY, z = (size_t)CP * RBZ, g = 1024;  // (256 features of gamma)
   static constexpr size_t offZ = NB * y, offG = offZ + NB * z, total = offG + NB * g;
 };
@@ -68,9 +69,11 @@ __device__ __forceinline__ bf16x8 ld_tr(const char *tile, int b0, int b1, int ro
   return __builtin_bit_cast(bf16x8, s8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
 }
 
-template <int KP, int CP, bool REV> __global__ void __launch_bounds__(kTh) segstate_kernel(SegArgs a) {
+template <int KP, int CP, bool REV>
+__global__ void __launch_bounds__((SegLayout<KP, CP>::threads)) segstate_kernel(SegArgs a) {
   using L = SegLayout<KP, CP>;
-  constexpr int NFT = KP / 64;   // 32-feature state tiles per wave
+  constexpr int FW = L::FW, kTh = L::threads;
+  constexpr int NFT = KP / (32 * FW);  // 32-feature state tiles per wave
   constexpr int NU = CP / 16;    // 16-row steps of the update
   constexpr int RBY = L::RBY, RBZ = L::RBZ, esz = 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -80,7 +83,7 @@ template <int KP, int CP, bool REV> __global__ void __launch_bounds__(kTh) segst
   // (forward every segment but the last, reverse every one but the first)
   const int e = id % (a.nseg - 1);
   const SegMap sm = seg_map(id / (a.nseg - 1), e + (REV ? 1 : 0), a.T, a.C, a.N, a.Ns);
-  const int w = wave_id() & 3, l = lane_id(), cw = w & 1, fw = w >> 1, g2 = l >> 5, j2 = l & 31;
+  const int w = wave_id() & (2 * FW - 1), l = lane_id(), cw = w & 1, fw = w >> 1, g2 = l >> 5, j2 = l & 31;
   const int K = a.K, V = a.V, C = a.C, N = sm.N, v0 = tile * kCols, col = v0 + 32 * cw + j2;
   const int64_t KV = (int64_t)K * V;
   auto elem = [&](int i, int r) {  // byte offset of state element r of tile i (past d_k or d_v: out of range)
@@ -172,7 +175,9 @@ template <int KP, int CP, bool REV> hipError_t launch_sp(const SegArgs &a, hipSt
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   (void)attr;
   const size_t lds = SegLayout<KP, CP>::total;
-  hipLaunchKernelGGL((segstate_kernel<KP, CP, REV>), dim3(a.BH * (a.nseg - 1) * a.ntiles), dim3(kTh), lds, st, a);
+  const int threads = SegLayout<KP, CP>::threads;
+  hipLaunchKernelGGL((segstate_kernel<KP, CP, REV>), dim3(a.BH * (a.nseg - 1) * a.ntiles),
+                     dim3(threads), lds, st, a);
   return hipGetLastError();
 }
 

@@ -1101,3 +1101,40 @@ def test_fp32_diagonal_general_form(io):
     for n in ("dq", "dk", "dv", "dlog_alpha", "dlog_beta", "dS0"):
         errs[n] = (heads(gr[n], idx), rg[n])
     judge(" ".join(map(str, ("fp32 diagonal, general form", io,))), errs, TOL[io])
+
+
+RAGGED = [
+    # key widths of every state-only variant (64, 128, 192, 256), a last chunk
+    # and a last segment that are shorter, partial value tiles and slabs
+    small_case("seg_K48_V80_C16", "bf16", 1, 1, 1000, 48, 80, 16, 16, 61, s0_std=0.1),
+    small_case("seg_K112_V208_C32", "bf16", 1, 1, 2100, 112, 208, 32, 16, 62, s0_std=0.1),
+    small_case("seg_K144_V304", "bf16", 1, 2, 1543, 144, 304, 64, 16, 63, s0_std=0.1),
+    small_case("seg_K256_V144", "bf16", 1, 1, 1999, 256, 144, 64, 16, 64, s0_std=0.1),
+    small_case("seg_f32_K80_V96_C32", "f32", 1, 2, 777, 80, 96, 32, 16, 65, s0_std=0.1),
+    small_case("seg_f32_K128_V48", "f32", 1, 1, 1090, 128, 48, 64, 16, 66, s0_std=0.1),
+]
+
+
+@pytest.mark.parametrize("cfg", RAGGED, ids=[c["name"] for c in RAGGED])
+def test_ragged_sequence_segments(cfg):
+    """Few heads and a length that is no multiple of the chunk: segments with a
+    shorter last one, S0 and dS_T, every output against the oracle; and the
+    same sequence on one segment, whose chunks outnumber the 64 up to which
+    the gate gradient's carry is summed in place (C = 16, 32)."""
+    g = gla()
+    inp = W.make_inputs(cfg, dST_std=0.1)
+    size = lambda n: g.workspace_bytes(*(cfg[x] for x in ("B", "H", "T", "dk", "dv", "chunk", "subchunk")),
+                                       W.torch_dtype(cfg["io"]), op=0, segments=n)
+    assert size(0) > size(1), "the shape is segmented"
+    o, ST, gr = run_gpu(inp, cfg["chunk"], cfg["subchunk"], want_state=True)
+    idx = list(range(cfg["B"] * cfg["H"]))
+    compare(inp, o, ST, gr, idx, cfg["io"], cfg["name"])
+    _, _, again = run_gpu(inp, cfg["chunk"], cfg["subchunk"], want_state=True, reuse=False)
+    for n in gr:
+        assert torch.equal(gr[n], again[n]), "reuse, " + n
+    d = to_dev(inp)
+    args = (d["q"], d["k"], d["v"], d["log_alpha"])
+    o1, ST1 = g.chunk_fwd(*args, cfg["chunk"], cfg["subchunk"], S0=d["S0"], output_final_state=True, segments=1)
+    g1 = g.chunk_bwd(*args, d["dO"], cfg["chunk"], cfg["subchunk"], S0=d["S0"], dST=d["dST"], want_dS0=True, segments=1)
+    torch.cuda.synchronize()
+    compare(inp, o1, ST1, g1, idx, cfg["io"], cfg["name"] + ", one segment")
