@@ -198,20 +198,6 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
   const auto rs_dkr = make_rsrc(a.dkr + ((int64_t)bh * T_ + t0) * K, fbytes);
   const int NG = (K + 63) / 64;
 
-  uint32_t nq[16], nk[16], nl[16];
-  auto issue_group = [&](int gi) {
-    const int f = 64 * gi + l;
-    const bool fv = f < K;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 16 * w + r;
-      const uint32_t off = fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u;
-      nq[r] = ld_el<T>(rs_q, off);
-      nk[r] = ld_el<T>(rs_k, off);
-      nl[r] = ld_el<T>(rs_la, off);
-    }
-  };
-
   // ---- 1. the chunk's dP, transposed back into rows (thread: C/4
   // consecutive t of one s)
   {
@@ -234,40 +220,52 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
     const bool fv = f < K;
     // the block's rows of q, k and the gate, for this lane's feature
     uint32_t rq[16], rk[16], rl[16], rr[16], rs[16];
-    issue_group(gi);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      rq[r] = nq[r];
-      rk[r] = nk[r];
-      rl[r] = nl[r];
+      const uint32_t off = fv ? (uint32_t)(((16 * w + r) * K + f) * esz) : 0x80000000u;
+      rq[r] = ld_el<T>(rs_q, off);
+      rk[r] = ld_el<T>(rs_k, off);
+      rl[r] = ld_el<T>(rs_la, off);
     }
     if (fv) sCar[w * 64 + l] = carry_part<NB>(a, bh, n, f, w);
-    float q[16], kk[16], c[16], la[PRE ? 16 : 1];
-    float run = 0.f;
+    // step decays and their running products: exp(Bloc) down the block's rows
+    // and exp(tot - Bloc) up them (formed again at the combine)
+    float q[16], kk[16], al[16];
+    float tot = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float x = el_f<T>(rl[r]);
-      if constexpr (PRE) la[r] = x = gate_la(x, a.inv_tau, fv && 16 * w + r < rv);
-      run += x;
-      c[r] = run;  // Bloc
+      if constexpr (PRE) x = gate_la(x, a.inv_tau, fv && 16 * w + r < rv);
+      tot += x;
+      al[r] = __expf(x);
       q[r] = el_f<T>(rq[r]);
       kk[r] = el_f<T>(rk[r]);
     }
-    const float tot = run;
     // (block sums and group tiles are read after B2; the previous group's
     // result tiles, which the group tiles overlay, were consumed before its B4)
     sTot[w * 64 + l] = tot;
 
     // operands of the orange blocks, feature-major
+    float run = 1.f;
 #pragma unroll
     for (int r = 0; r < 16; r += 4) {
-      f4 qz, kz;
+      f4 qz;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        qz[u] = q[r + u] * __expf(c[r + u]);
-        kz[u] = kk[r + u] * __expf(tot - c[r + u]);
+        run *= al[r + u];
+        qz[u] = q[r + u] * run;
       }
       *(f4 *)(sQz + l * LDD + 16 * w + r) = qz;
+    }
+    run = 1.f;
+#pragma unroll
+    for (int r = 12; r >= 0; r -= 4) {
+      f4 kz;
+#pragma unroll
+      for (int u = 3; u >= 0; --u) {
+        kz[u] = kk[r + u] * run;
+        run *= al[r + u];
+      }
       *(f4 *)(sKz + l * LDD + 16 * w + r) = kz;
     }
 
@@ -275,7 +273,8 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
     // row to row as the product of the step decays (dec[j] at row i), shared
     // by both sums (dP rows read as wave-uniform broadcasts).  One exponential
     // per row instead of one per pair: 339 to 304 us on 16 x 16 heads of 2048
-    // steps at d_k = 128, 94 to 89 us on 8 x 4 heads at d_k = 256 (bf16).
+    // steps at d_k = 128, 94 to 89 us on 8 x 4 heads at d_k = 256 (bf16; when
+    // this kernel still ran between the sweeps).
     float dqp[16], dkp[16], dec[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) dqp[r] = dkp[r] = 0.f;
@@ -289,12 +288,9 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int u = 0; u < 4; ++u) p[4 * j4 + u] = v4[u];
       }
-      float x = el_f<T>(rl[i]);
-      if constexpr (PRE) x = la[i];
-      const float al = __expf(x);
 #pragma unroll
       for (int j = 0; j < i; ++j) {
-        dec[j] *= al;
+        dec[j] *= al[i];
         const float t = p[j] * dec[j];
         dqp[i] += t * kk[j];
         dkp[j] += t * q[i];
@@ -382,20 +378,22 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
       }
     // (the wave reads back only what it wrote: LDS keeps one wave's accesses in order)
     float dA[16];
+    run = 1.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int row = 16 * w + r;
-      const float dq = __builtin_bit_cast(float, rr[r]) + (__expf(c[r]) * oqw[l * LDO + r] + dqp[r]);
-      const float dk = __builtin_bit_cast(float, rs[r]) + (__expf(tot - c[r]) * okw[l * LDO + r] + dkp[r]);
-      const uint32_t off = fv ? (uint32_t)((row * K + f) * esz) : 0x80000000u;
-      st_el<T>(rs_dq, off, dq);
-      st_el<T>(rs_dk, off, dk);
-      dA[r] = q[r] * dq - kk[r] * dk;
+      run *= al[r];
+      const float dq = __builtin_bit_cast(float, rr[r]) + (run * oqw[l * LDO + r] + dqp[r]);
+      st_el<T>(rs_dq, fv ? (uint32_t)(((16 * w + r) * K + f) * esz) : 0x80000000u, dq);
+      dA[r] = q[r] * dq;
     }
-    float sa = 0.f;
+    run = 1.f;
+    float sa = 0.f;  // in-chunk reverse sums of q dq - k dk
 #pragma unroll
     for (int r = 15; r >= 0; --r) {
-      sa += dA[r];
+      const float dk = __builtin_bit_cast(float, rs[r]) + (run * okw[l * LDO + r] + dkp[r]);
+      run *= al[r];
+      st_el<T>(rs_dk, fv ? (uint32_t)(((16 * w + r) * K + f) * esz) : 0x80000000u, dk);
+      sa += dA[r] - kk[r] * dk;
       dA[r] = sa;
     }
     sTA[w * 64 + l] = sa;
