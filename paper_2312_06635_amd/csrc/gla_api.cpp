@@ -305,10 +305,10 @@ GLA_EXPORT gla_status gla_chunk_bwd(const gla_problem *prob, const void *q, cons
   if (run(2)) {
     // the final-state gradients of the inner segments, then the sweeps
     if (e == hipSuccess && nseg > 1) e = gla::launch_seg_states(s, sg, true, dO, dS_T, w, hs);
-    if (e == hipSuccess) e = gla::launch_key_sweeps(s, sg, q, k, log_alpha, v, S0, dO, dS_T, w, hs, ng);
+    if (e == hipSuccess) e = gla::launch_key_sweeps(s, sg, q, k, log_alpha, v, S0, dO, dS_T, dq, dk, w, hs, ng);
   }
-  if (e == hipSuccess && run(3))
-    e = gla::launch_bwd_intra(s, sg, q, k, log_alpha, dS_T || nseg > 1, dq, dk, dlog_alpha, w, hs, ng);
+  if (e == hipSuccess && run(3) && !ng)
+    e = gla::launch_bwd_intra(s, sg, q, k, log_alpha, dS_T || nseg > 1, dq, dk, dlog_alpha, w, hs);
   if (e == hipSuccess && run(5)) e = gla::launch_bwd_dv(s, sg, dO, nullptr, dS_T, dv, dS0, w, hs);
   return hip_status(e);
 }
@@ -345,9 +345,10 @@ GLA_EXPORT gla_status gla_chunk_bwd_general(const gla_problem *prob, const void 
   if (run(1) && !(prob->flags & GLA_FLAG_REUSE_FWD_WORKSPACE))
     e = gla::launch_prep(s, q, k, log_alpha, w, hs);
   if (e == hipSuccess && run(2)) e = gla::launch_beta_prep(s, v, dO, log_beta, w, hs);
-  if (e == hipSuccess && run(3)) e = gla::launch_key_sweeps(s, one, q, k, log_alpha, w.Vh, S0, w.Oh, dS_T, w, hs, false, true);
+  if (e == hipSuccess && run(3)) e = gla::launch_key_sweeps(s, one, q, k, log_alpha, w.Vh, S0, w.Oh, dS_T, dq, dk, w, hs,
+                               false, true);
   if (e == hipSuccess && run(4))
-    e = gla::launch_bwd_intra(s, one, q, k, log_alpha, dS_T != nullptr, dq, dk, dlog_alpha, w, hs, false);
+    e = gla::launch_bwd_intra(s, one, q, k, log_alpha, dS_T != nullptr, dq, dk, dlog_alpha, w, hs);
   if (e == hipSuccess && run(6)) e = gla::launch_bwd_dv(s, one, dO, log_beta, dS_T, dv, dS0, w, hs);
   if (e == hipSuccess && run(7) && dlog_beta)
     e = gla::launch_beta_grad(s, o, dO, v, dv, dlog_beta, w, hs);

@@ -430,8 +430,8 @@ template <typename T> __device__ __forceinline__ f4 mma2s(f4 acc, const Split<T>
 // split into bf16 hi + lo once per chunk, q and k enter exactly (no
 // factorised operands, no per-feature exponentials).  The gate gradient is
 // formed as in the per-feature kernel and, for a scalar gate, summed over the
-// features; NG (no gate) skips it.
-template <typename T, int C, bool PRE, bool NG>
+// features.
+template <typename T, int C, bool PRE>
 __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per_eu(2)))
 intra_plain_kernel(IntraArgs a) {
   using L = IntraLayout<C>;
@@ -458,7 +458,7 @@ intra_plain_kernel(IntraArgs a) {
 
   // chunk-local inclusive cumsum of log gamma in units of log2, lane t = step t
   float c2 = 0.f, z = 0.f;  // (z: the gate argument of this lane's step)
-  if constexpr (!NG) {
+  {
     // (an absent gate whose gradient is wanted reads as log alpha = 0 from an
     // empty range; the per-feature dA below is then that gradient's share)
     const auto rs_la = make_rsrc(a.la ? (const T *)a.la + (int64_t)bh * T_ + t0 : qc,
@@ -479,7 +479,7 @@ intra_plain_kernel(IntraArgs a) {
     constexpr int PER = C / 4;
     const int e0 = (int)threadIdx.x * PER, sc = e0 / C, tb = e0 % C;
     const float *src = a.dP + ((int64_t)bh * a.N + n) * C * C + e0;
-    const float cs = NG ? 0.f : __shfl(c2, sc);
+    const float cs = __shfl(c2, sc);
 #pragma unroll
     for (int u = 0; u < PER; u += 4) {
       const f4 x = *(const f4 *)(src + u);
@@ -487,7 +487,7 @@ intra_plain_kernel(IntraArgs a) {
       for (int r = 0; r < 4; ++r) {
         const int t = tb + u + r;
         float v = x[r];
-        if constexpr (!NG) {
+        {
           // (the cross-lane read runs in every lane: a lane that skipped it
           // would hand its readers no value)
           const float ct = __shfl(c2, t);
@@ -540,7 +540,7 @@ intra_plain_kernel(IntraArgs a) {
       rr[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dqr, off, 0, 0);
       rs[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_dkr, off, 0, 0);
     }
-    if constexpr (!NG) {
+    {
       if (fv) sCar[w * 64 + l] = carry_part<NB>(a, bh, n, f, w);
     }
     float q[16], kk[16];
@@ -615,7 +615,7 @@ intra_plain_kernel(IntraArgs a) {
       st_el<T>(rs_dk, off, dk);
       dA[r] = q[r] * dq - kk[r] * dk;
     }
-    if constexpr (!NG) {
+    {
       float sa = 0.f;
 #pragma unroll
       for (int r = 15; r >= 0; --r) {
@@ -644,7 +644,7 @@ intra_plain_kernel(IntraArgs a) {
     }
     __syncthreads();  // result tiles and carries consumed before the next group's overlay them
   }
-  if constexpr (!NG) {
+  {
     if (a.sg && a.dla) {
       // the gate is shared by the features: its gradient is their sum, in a fixed order
       float x = 0.f;
@@ -697,30 +697,29 @@ hipError_t launch_intra_t(const Shape &s, const IntraArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename T, int C, bool PRE, bool NG>
+template <typename T, int C, bool PRE>
 hipError_t launch_intra_plain(const Shape &s, const IntraArgs &a, hipStream_t st) {
-  static const hipError_t attr = hipFuncSetAttribute((const void *)intra_plain_kernel<T, C, PRE, NG>,
+  static const hipError_t attr = hipFuncSetAttribute((const void *)intra_plain_kernel<T, C, PRE>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   (void)attr;
-  hipLaunchKernelGGL((intra_plain_kernel<T, C, PRE, NG>), dim3(s.N, s.BH), dim3(64 * (C / 16)), IntraLayout<C>::total,
+  hipLaunchKernelGGL((intra_plain_kernel<T, C, PRE>), dim3(s.N, s.BH), dim3(64 * (C / 16)), IntraLayout<C>::total,
                      st, a);
   return hipGetLastError();
 }
 
 template <typename T, int C>
-hipError_t launch_intra_c(const Shape &s, const IntraArgs &a, hipStream_t st, bool ng) {
-  if (ng) return launch_intra_plain<T, C, false, true>(s, a, st);
+hipError_t launch_intra_c(const Shape &s, const IntraArgs &a, hipStream_t st) {
   if (a.sg || !a.la)
-    return a.inv_tau != 0.f ? launch_intra_plain<T, C, true, false>(s, a, st)
-                            : launch_intra_plain<T, C, false, false>(s, a, st);
+    return a.inv_tau != 0.f ? launch_intra_plain<T, C, true>(s, a, st)
+                            : launch_intra_plain<T, C, false>(s, a, st);
   return a.inv_tau != 0.f ? launch_intra_t<T, C, true>(s, a, st) : launch_intra_t<T, C, false>(s, a, st);
 }
 
 template <typename T>
-hipError_t launch_intra_io(const Shape &s, const IntraArgs &a, hipStream_t st, bool ng) {
-  if (s.C == 16) return launch_intra_c<T, 16>(s, a, st, ng);
-  if (s.C == 32) return launch_intra_c<T, 32>(s, a, st, ng);
-  return launch_intra_c<T, 64>(s, a, st, ng);
+hipError_t launch_intra_io(const Shape &s, const IntraArgs &a, hipStream_t st) {
+  if (s.C == 16) return launch_intra_c<T, 16>(s, a, st);
+  if (s.C == 32) return launch_intra_c<T, 32>(s, a, st);
+  return launch_intra_c<T, 64>(s, a, st);
 }
 
 }  // namespace
@@ -730,7 +729,7 @@ size_t lds_bwd_intra(const Shape &s) {
 }
 
 hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, bool has_dST,
-                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng) {
+                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st) {
   IntraArgs a{};
   a.q = q; a.k = k; a.la = la; a.dP = w.dP; a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk;
   a.cST = has_dST ? w.cST : nullptr;
@@ -739,7 +738,7 @@ hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const
   a.nseg = sg.n; a.Ns = sg.Ns;
   a.sg = s.sgate ? 1 : 0;
   a.inv_tau = s.inv_tau;
-  if (!ng && dla && a.Ns > kCarryDirect) {
+  if (dla && a.Ns > kCarryDirect) {
     // (per workgroup the direct sum reads up to Ns rows of both arrays: beyond
     // a few dozen that costs more than this pass over them)
     hipLaunchKernelGGL(carry_scan_kernel, dim3((s.K + 63) / 64, s.BH * sg.n), dim3(64), 0, st, a, w.carry);
@@ -747,7 +746,7 @@ hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const
     if (e != hipSuccess) return e;
     a.carry = w.carry;
   }
-  return s.io == IO_BF16 ? launch_intra_io<bf16>(s, a, st, ng) : launch_intra_io<float>(s, a, st, ng);
+  return s.io == IO_BF16 ? launch_intra_io<bf16>(s, a, st) : launch_intra_io<float>(s, a, st);
 }
 
 }  // namespace gla

@@ -56,7 +56,12 @@
 // 1 and the gated operands are k and q themselves, so the factor phase only
 // stages k (q), the partials need no scaling, the state needs no decay, and
 // with no gate gradient to protect the state and update operands are used as
-// single bf16 values (as the forward's inter-chunk products use them).
+// single bf16 values (as the forward's inter-chunk products use them).  The
+// intra-chunk terms are then dP K and dP^T Q with the gated operand that is in
+// LDS already, so each key tile forms dP for itself and the sweeps write dq and
+// dk: no fp32 terms or dP go through memory and no in-chunk kernel follows.
+// Forward + backward, us, against the terms handed over (bf16): 32 x 16 heads x
+// 2048 at 64/64 909 -> 660; 16 x 16 x 2048 at 128/128 1061 (the start) -> 681.
 //
 // General form (GB; App. C, a value-side gate beta as well): v and dO arrive
 // as Vh = V (.) exp(-E) and Oh = dO (.) exp(E) (E the chunk-local cumsum of
@@ -91,7 +96,8 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 struct KsArgs {
   const void *q, *k, *la, *v, *dO;
   const float *S0, *dST;
-  float *dqr, *dkr;  // [BH][T][K] fp32 dq_inter, dk_inter
+  float *dqr, *dkr;  // [BH][T][K] fp32 dq_inter, dk_inter (not NG)
+  void *dq, *dk;     // [BH][T][K] io: the gradients themselves (NG)
   float *tq, *tk;    // [BH][N][K] fp32 per chunk sums of q (.) dq_inter, k (.) dk_inter (not NG)
   float *dP;         // [BH][N][C][C] fp32 (dO V^T) (.) M per chunk, stored transposed ([s][t])
   float *cST;        // [BH][nseg][K] rowsum(S_T (.) dS_T) per segment (not written with one segment and no dST)
@@ -346,7 +352,7 @@ template <typename T, int CP, int NSL, bool REV, bool PRE, bool GB, bool NG>
 __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   using L = KsLayout<T, CP>;
   constexpr int NST = CP / 16, NTT = CP / 32, RPT = L::RPT, UM = CP / 4 - 1;
-  constexpr int NDT = CP == 64 ? 3 : 1;  // dP tiles on or below the diagonal, one per wave 0..NDT-1
+  constexpr int NDT = CP == 64 ? 3 : 1;  // dP tiles that hold kept entries, one per wave 0..NDT-1
   constexpr bool SPLIT = sizeof(T) == 2 && !NG;
   // buffer b: X tile at b * 2 slab, Z tile right after it
   T *sX0 = (T *)smem, *sZ0 = (T *)(smem + L::slab);
@@ -519,6 +525,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   };
 
   float *outh = (REV ? a.dkr : a.dqr) + row0 * K;
+  T *gradh = (T *)(REV ? a.dk : a.dq) + row0 * K;  // (NG)
   float *toth = (REV ? a.tk : a.tq) + chunk0 * K;
   float *dPg = a.dP + chunk0 * C * C;
   // the chunk sums published by the previous boundary
@@ -527,12 +534,15 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
       if (tid < kKF && fv) toth[(int64_t)n * K + kf] = (sTot[tid] + sTot[kKF + tid]) + (sTot[2 * kKF + tid] + sTot[3 * kKF + tid]);
     }
   };
-  // dP tiles (dq sweep): waves 0..NDT-1 each accumulate one whole 32x32 tile (t
-  // rows 32 tr.., s columns 32 tc..: T00, T10, T11) over every slab of the
-  // chunks this key tile forms dP for; wave NDT writes the zero tile above the
-  // diagonal
-  const bool dpw = !REV && w < NDT;
-  const int tr = (w == 1 || w == 2) ? 1 : 0, tc = w == 2 ? 1 : 0;
+  // Tiles of X Z^T over every slab of a chunk (waves 0..NDT-1: rows 32 tr..,
+  // columns 32 tc..).  dq sweep: dP = dO V^T, kept for column <= row, so T00,
+  // T10, T11; formed for the chunks of this key tile and handed over, wave NDT
+  // writing the zero tile above the diagonal.  NG: both sweeps form it for
+  // every chunk (dk: V dO^T = dP^T, kept for column >= row: T00, T01, T11) and
+  // multiply it with G themselves.
+  const bool dpw = (NG || !REV) && w < NDT;
+  const int tr = NG && REV ? (w == 2 ? 1 : 0) : ((w == 1 || w == 2) ? 1 : 0);
+  const int tc = NG && REV ? ((w == 1 || w == 2) ? 1 : 0) : (w == 2 ? 1 : 0);
   constexpr int RB = row_bytes<T>();
   const int pA = lb0 + 32 * tr * RB, pB = lb0 + 32 * tc * RB;
   const int pA1 = lb1 + 32 * tr * RB, pB1 = lb1 + 32 * tc * RB;
@@ -553,7 +563,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     const int n = chunk_of(it), t0 = n * C;
     if (it > 0) store_totals(chunk_of(it - 1));
     const float gj = NG ? 1.f : sG[j];
-    const bool mine = dpw && n % a.KT == kt;  // this wave forms a tile of the chunk's dP
+    const bool mine = dpw && (NG || n % a.KT == kt);  // this wave forms a tile of the chunk's dP
     f16v acc[2], accP;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = accP[e] = 0.f;
@@ -593,7 +603,15 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         S[sl] = mma32<T>(S[sl], zf, ld_row32<T>(sBh, L::LDTB, 0, 16 * u));
         if constexpr (SPLIT) S[sl] = mma32<T>(S[sl], zf, ld_row32<T>(sBl, L::LDTB, 0, 16 * u));
       }
-      if constexpr (!REV) {
+      if constexpr (NG) {
+        // (transposed, so that a lane holds consecutive columns of a row)
+        if (mine) {
+          const int steps = min(kVS, V - sl * kVS) / 16;
+#pragma unroll 4
+          for (int st = 0; st < steps; ++st)
+            accP = mma32<T>(accP, ld_slab_row<T>(sZ, pB, pB1, 0, 16 * st), ld_slab_row<T>(sX, pA, pA1, 0, 16 * st));
+        }
+      } else if constexpr (!REV) {
         if (mine) {
 #pragma unroll
           for (int st = 0; st < kVS / 16; ++st)
@@ -614,7 +632,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     }
 
     // ---- dP of this key tile's chunks: masked, handed over transposed ([s][t])
-    if constexpr (!REV) {
+    if constexpr (!REV && !NG) {
       if (mine || (CP == 64 && w == NDT && n % a.KT == kt)) {
         const bool zero_tile = !dpw;
         const int rt = zero_tile ? 0 : tr, ct = zero_tile ? 1 : tc;
@@ -634,7 +652,56 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     // ---- the partials into the buffer of the chunk's last slab (the other
     // one holds the next chunk's first slab): unit u (four rows) of feature j
     // at unit u ^ (j mod CP/4); the next chunk's factor part 1 alongside
-    float *sRed = (float *)(smem + (((it * NSL + NSL - 1) & 1) ? 2 * L::slab : 0));
+    char *last = smem + (((it * NSL + NSL - 1) & 1) ? 2 * L::slab : 0);
+    float *sRed = (float *)last;
+    if constexpr (NG) {
+      // ---- intra-chunk term: M = the chunk's masked X Z^T (rows x columns, hi
+      // and lo for bf16; 16-byte chunk c of row r at c ^ (r mod 8)) through the
+      // buffer of the chunk's last slab, then acc += M G, wave w taking M's
+      // columns 16 w .. +16 (the waves' partials are summed below anyway)
+      constexpr int RM = CP * (int)sizeof(T), E = 16 / (int)sizeof(T);
+      auto at = [&](int row, int col) {
+        return row * RM + (((col / E) ^ (row & (RM / 16 - 1) & 7)) << 4) + (col % E) * (int)sizeof(T);
+      };
+      char *sMh = last, *sMl = last + CP * RM;
+      if (dpw) {
+        const int row = 32 * tr + j;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int c4 = 32 * tc + 8 * b + 4 * g;
+          T hi[4], lo[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float x = (REV ? c4 + r >= row : c4 + r <= row) ? accP[4 * b + r] : 0.f;
+            hi[r] = cvt<T>(x);
+            lo[r] = cvt<T>(x - (float)hi[r]);
+          }
+          store_rows<T, 4>((T *)(sMh + at(row, c4)), hi);
+          if constexpr (sizeof(T) == 2) store_rows<T, 4>((T *)(sMl + at(row, c4)), lo);
+        }
+      }
+      __syncthreads();
+      if (w < NST) {
+        const frag_t<T> gf = ld_row32<T>(sBh, L::LDTB, 0, 16 * w);
+        auto ld_m = [&](const char *m, int th) -> frag_t<T> {
+          const int row = 32 * th + j, col = 16 * w + 8 * g;
+          if constexpr (sizeof(T) == 2) {
+            return *(const bf16x8 *)(m + at(row, col));
+          } else {
+            const f4 x = *(const f4 *)(m + at(row, col)), y = *(const f4 *)(m + at(row, col + 4));
+            return f8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+          }
+        };
+#pragma unroll
+        for (int th = 0; th < NTT; ++th) {
+          // (tiles without kept entries are not formed)
+          if (REV ? 16 * w + 15 < 32 * th : 16 * w >= 32 * th + 32) continue;
+          acc[th] = mma32<T>(acc[th], ld_m(sMh, th), gf);
+          if constexpr (sizeof(T) == 2) acc[th] = mma32<T>(acc[th], ld_m(sMl, th), gf);
+        }
+      }
+      __syncthreads();  // M consumed before the partials overlay it
+    }
 #pragma unroll
     for (int th = 0; th < NTT; ++th)
 #pragma unroll
@@ -650,9 +717,10 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     // (rows past the sequence end, past the chunk or of absent features fall
     // outside the buffer range and are dropped)
     {
-      const auto rs = make_rsrc(outh + (int64_t)t0 * K, rsrc_bytes((int64_t)(sm.rows - t0) * K * 4));
+      const auto rs = NG ? make_rsrc(gradh + (int64_t)t0 * K, rsrc_bytes((int64_t)(sm.rows - t0) * K * esz))
+                         : make_rsrc(outh + (int64_t)t0 * K, rsrc_bytes((int64_t)(sm.rows - t0) * K * 4));
       float tot = 0.f;
-      uint32_t oo = ooff;
+      uint32_t oo = NG ? eoff : ooff;
       asm volatile("" : "+v"(oo));
 #pragma unroll
       for (int i4 = 0; i4 < RPT / 4; ++i4) {
@@ -667,7 +735,8 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
             x *= scale[i];
             tot += x * oth[i];
           }
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rs, oo + (uint32_t)(i * K * 4), 0, 0);
+          if constexpr (NG) st_elem<T>(rs, oo + (uint32_t)(i * K * esz), cvt<T>(x));
+          else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rs, oo + (uint32_t)(i * K * 4), 0, 0);
         }
       }
       if constexpr (!NG) {
@@ -803,11 +872,11 @@ size_t ks_state_elems(const Shape &s) {
 }
 
 hipError_t launch_key_sweeps(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, const void *v,
-                             const float *S0, const void *dO, const float *dST, const Work &w, hipStream_t st, bool ng,
-                             bool gb_on) {
+                             const float *S0, const void *dO, const float *dST, void *dq, void *dk, const Work &w,
+                             hipStream_t st, bool ng, bool gb_on) {
   KsArgs a{};
   a.q = q; a.k = k; a.la = la; a.v = v; a.dO = dO; a.S0 = S0; a.dST = dST;
-  a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk; a.dP = w.dP; a.cST = w.cST;
+  a.dq = dq; a.dk = dk; a.dqr = w.dqr; a.dkr = w.dkr; a.tq = w.tq; a.tk = w.tk; a.dP = w.dP; a.cST = w.cST;
   if (gb_on) { a.gbv = w.gb; a.Sb = w.Sb; a.Db = w.Db; }
   a.BH = s.BH; a.T = s.T; a.K = s.K; a.V = s.V; a.C = s.C; a.Nh = s.N;
   a.nseg = sg.n; a.Ns = sg.Ns; a.Sseg = w.Sseg; a.dSseg = w.dSseg;

@@ -66,17 +66,17 @@ hipError_t launch_seg_states(const Shape &s, const Segs &sg, bool rev, const voi
                              hipStream_t st);
 // The key sweeps, side by side in one launch: w.dqr, w.tq, w.dP, w.cST (dq) and
 // w.dkr, w.tk (dk).
-// ng: no gate and no gate gradient wanted (la and the backward's dla NULL;
-// w.tq, w.tk are then not written)
+// ng: no gate and no gate gradient wanted (la and the backward's dla NULL);
+// the sweeps then write dq and dk themselves and nothing else
 // gb_on: the general form (v, dO are then w.Vh, w.Oh; the states decay by
 // w.gb); w.cpart as well.
 hipError_t launch_key_sweeps(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, const void *v,
-                             const float *S0, const void *dO, const float *dST, const Work &w, hipStream_t st, bool ng,
-                             bool gb_on = false);
-// The in-chunk terms of the backward, after both key sweeps: dq, dk and (unless
-// NULL) dla.  has_dST: w.cST holds the final-state terms.
+                             const float *S0, const void *dO, const float *dST, void *dq, void *dk, const Work &w,
+                             hipStream_t st, bool ng, bool gb_on = false);
+// The in-chunk terms of the backward, after both key sweeps (not with ng): dq,
+// dk and (unless NULL) dla.  has_dST: w.cST holds the final-state terms.
 hipError_t launch_bwd_intra(const Shape &s, const Segs &sg, const void *q, const void *k, const void *la, bool has_dST,
-                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st, bool ng);
+                            void *dq, void *dk, void *dla, const Work &w, hipStream_t st);
 // lb: log beta of the general form (nullable)
 hipError_t launch_bwd_dv(const Shape &s, const Segs &sg, const void *dO, const void *lb, const float *dST, void *dv,
                          float *dS0, const Work &w, hipStream_t st);
