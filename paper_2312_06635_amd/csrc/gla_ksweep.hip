@@ -40,6 +40,14 @@
 // took 169 + 197 us; side by side as here 233 us (and with the slabs staged
 // through registers 252 us).
 //
+// Only dP needs another wave's columns of a slab, so each wave copies its own
+// 32 columns (LDS DMA, counted waits) into its own two slots and meets the
+// others once per chunk only, or per slab where a chunk's dP is formed.
+// Forward + backward against slabs shared by the workgroup, with a barrier
+// each: 128 heads x 2048 at 128/256 with the gate epilogue 938 -> 922 us, 512 x
+// 2048 at 128/128 1286 -> 1253 us, 512 x 2048 at 64/64 without a gate 658 ->
+// 654 us, 32 x 2048 at 256/512 532 us either way.
+//
 // Accumulator row m holds value 16 (m / 16) + 8 ((m / 4) % 2) + 4 ((m / 8) % 2)
 // + m % 4 of the wave's 32, which makes the 8 values a lane holds for one
 // 16-deep step contiguous: the tile is directly an operand of the next
@@ -119,15 +127,13 @@ template <typename T, int CP> struct KsLayout {
   // eight consecutive rows are 8/16-byte LDS accesses.
   static constexpr int LDTB = CP + (sizeof(T) == 2 ? 8 : 4);
   static constexpr int LDRG = kRG + 4;  // row-group sums [32][kRG]
-  static constexpr size_t slab = sizeof(T) * CP * kVS;
-  // slab buffer b: the X tile at 2 b slab, the Z tile after it
-  static constexpr size_t offBh = 4 * slab;                         // gated update operand (hi)
+  // A wave's own two slab slots, each its 32 columns of X and of Z.  The chunk's
+  // partial sums ([32 features][CP rows] fp32 per wave, 16-byte units
+  // XOR-swizzled per feature) overlie the wave's slot of the chunk's last slab.
+  static constexpr size_t sub = sizeof(T) * CP * 32, slot = 2 * sub, wave = 2 * slot;
+  static_assert(4 * kKF * CP <= slot, "partials fit over a slot");
+  static constexpr size_t offBh = kNW * wave;                       // gated update operand (hi)
   static constexpr size_t offBl = offBh + sizeof(T) * kKF * LDTB;   // (lo, bf16 only)
-  // per-wave partial sums [kNW][32 features][CP rows] fp32, 16-byte units
-  // XOR-swizzled per feature: aliased over the slab buffer of the chunk's last
-  // slab, which is free from that slab's barrier until the next slab store
-  // into it (two barriers later)
-  static_assert(4 * kNW * kKF * CP <= 2 * slab, "partials fit over a slab buffer");
   static constexpr size_t offRg = offBl + (sizeof(T) == 2 ? sizeof(T) * kKF * LDTB : 0);
   static constexpr size_t offG = offRg + 4 * kKF * LDRG;            // gamma [32]
   static constexpr size_t offTot = offG + 4 * kKF;                  // per-wave sums [kNW][32]
@@ -162,17 +168,15 @@ __device__ __forceinline__ int perm32(int m) {
 // Value offset of accumulator element e of lane group g.
 __device__ __forceinline__ int acc_value(int e, int g) { return perm32(8 * (e >> 2) + 4 * g + (e & 3)); }
 
-// Slab tiles: rows of RB bytes (128 values) whose 16-byte chunk c is stored at
-// chunk c ^ swz(row).  The swizzle permutes the low four chunk bits only and
-// the row offset starts above them, so the byte offset of (row r0 + rr, chunk
-// c0 / E + cc), with r0 a multiple of 16 and c0 a multiple of 16 values above
-// the lane's own chunk bits cc, splits into a per-lane part XOR a wave-uniform
-// column part, plus r0 RB: each lane keeps one base per read pattern and every
-// read is one XOR (or none) away from it.
-template <typename T> constexpr int row_bytes() { return kVS * (int)sizeof(T); }
-__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-struct SlabSwz {
-  static __device__ __forceinline__ int swz(int row) { return gla::swz(row); }
+// A wave's slab tiles: rows of RB bytes (32 values) whose 16-byte chunk c is
+// stored at chunk c ^ swz(row), which gives 16 rows of one chunk index (the row
+// reads) disjoint banks; four whole rows (the transpose reads) have them
+// anyway.  Only the low four row bits enter and column steps are whole chunks,
+// so each lane keeps one base per read pattern and every read is one XOR and a
+// row offset away from it.
+template <typename T> constexpr int row_bytes() { return 32 * (int)sizeof(T); }
+template <typename T> struct SlabSwz {
+  static __device__ __forceinline__ int swz(int row) { return sizeof(T) == 2 ? (row >> 2) & 3 : (row >> 1) & 7; }
 };
 
 // Lane base of a row fragment (rows r0 + j, columns c0 + 8g; for fp32 half h
@@ -180,7 +184,7 @@ struct SlabSwz {
 template <typename T> __device__ __forceinline__ int row_lane_base(int h) {
   const int l = lane_id(), j = l & 31, g = l >> 5;
   const int ch = sizeof(T) == 2 ? g : 2 * g + h;
-  return j * row_bytes<T>() + ((ch ^ swz(j)) << 4);
+  return j * row_bytes<T>() + ((ch ^ SlabSwz<T>::swz(j)) << 4);
 }
 
 // Row fragment from a slab: lane (g, j) gets X[r0 + j][c0 + 8g + i].
@@ -207,7 +211,7 @@ template <typename T> __device__ __forceinline__ int tr_lane_base(int x4) {
   const int l = lane_id(), L = l & 15, jh = (l >> 4) & 1, g = l >> 5;
   const int row = 8 * g + (L >> 2) + x4;
   const int ch = 2 * jh + (L & 1);
-  return row * row_bytes<T>() + ((ch ^ swz(row)) << 4) + 8 * ((L >> 1) & 1);
+  return row * row_bytes<T>() + ((ch ^ SlabSwz<T>::swz(row)) << 4) + 8 * ((L >> 1) & 1);
 }
 template <typename T>
 __device__ __forceinline__ frag_t<T> ld_slab_col_perm(const T *X, int lt0, int lt1, int r0, int c0) {
@@ -224,7 +228,7 @@ __device__ __forceinline__ frag_t<T> ld_slab_col_perm(const T *X, int lt0, int l
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int row = r0 + 8 * g + i;
-      r[i] = X[row * (row_bytes<T>() / 4) + (((col >> 2) ^ swz(row)) << 2) + (col & 3)];
+      r[i] = X[row * (row_bytes<T>() / 4) + (((col >> 2) ^ SlabSwz<T>::swz(row)) << 2) + (col & 3)];
     }
     return r;
   }
@@ -354,9 +358,6 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   constexpr int NST = CP / 16, NTT = CP / 32, RPT = L::RPT, UM = CP / 4 - 1;
   constexpr int NDT = CP == 64 ? 3 : 1;  // dP tiles that hold kept entries, one per wave 0..NDT-1
   constexpr bool SPLIT = sizeof(T) == 2 && !NG;
-  // buffer b: X tile at b * 2 slab, Z tile right after it
-  T *sX0 = (T *)smem, *sZ0 = (T *)(smem + L::slab);
-  T *sX1 = (T *)(smem + 2 * L::slab), *sZ1 = (T *)(smem + 3 * L::slab);
   T *sBh = (T *)(smem + L::offBh), *sBl = (T *)(smem + L::offBl);
   float *sRg = (float *)(smem + L::offRg), *sG = (float *)(smem + L::offG);
   float *sTot = (float *)(smem + L::offTot), *sOr = (float *)(smem + L::offOr);
@@ -440,19 +441,23 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         gbr[i] = __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)((tid + kKT * i) * 4), 0, 0));
     }
   };
-  TileDma<CP, row_bytes<T>(), kKT, SlabSwz> dma;
-  dma.init(w, V * esz, C, row_bytes<T>());
+  // Slabs: each wave copies and multiplies its own 32 columns, two slabs deep,
+  // with no barrier: a tile is copied over as soon as its products have read
+  // it, so its successor but one has the whole next slab to arrive.
+  TileDma<CP, row_bytes<T>(), 64, SlabSwz<T>> dma;
+  dma.init(0, V * esz, C, row_bytes<T>());
+  constexpr int ND = decltype(dma)::NV;  // copies per tile
   const uint32_t lds0 = lds_address(smem);
   const int NQ = N * NSL;
   auto chunk_of = [&](int it) { return REV ? N - 1 - it : it; };
-  // slab q into its buffer (past the last slab: the last one again)
-  auto fetch_slab = [&](int q) {
+  auto slot_of = [&](int wv, int q) { return smem + wv * L::wave + (q & 1) * L::slot; };
+  // wave's tile (0: X, 1: Z) of slab q into its slot (past the last slab: the last one again)
+  auto fetch_slab = [&](int q, int part) {
     const int qc = min(q, NQ - 1);
-    const int it = qc / NSL, sl = qc - it * NSL, t0 = chunk_of(it) * C, c0 = sl * kVS;
+    const int it = qc / NSL, sl = qc - it * NSL, t0 = chunk_of(it) * C, c0 = sl * kVS + 32 * w;
     const uint32_t bytes = rsrc_bytes(((int64_t)(sm.rows - t0) * V - c0) * esz);
-    const uint32_t dst = lds0 + ((q & 1) ? 2 * (uint32_t)L::slab : 0u);
-    dma.load(xh + (int64_t)t0 * V + c0, bytes, dst, w, (V - c0) * esz);
-    dma.load(zh + (int64_t)t0 * V + c0, bytes, dst + (uint32_t)L::slab, w, (V - c0) * esz);
+    const uint32_t dst = lds0 + (uint32_t)(w * L::wave + (q & 1) * L::slot + part * L::sub);
+    dma.load((part == 0 ? xh : zh) + (int64_t)t0 * V + c0, bytes, dst, 0, (V - c0) * esz);
   };
 
   // ---- gate factors of a chunk, in two parts around a barrier (the row-group
@@ -513,6 +518,10 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         lo[i] = cvt<T>(x - (float)hi[i]);
         scale[i] = REV ? gam[i] : lam[i];
         oth[i] = elem_f<T>(fo[i]);
+        // (converted here: left to the combine, the raw values outlive the next
+        // fetch, which then costs a copy of its results, and with it a wait for
+        // every load in flight)
+        asm volatile("" : "+v"(oth[i]));
       }
       if (rg == 0) sG[fk] = eg;  // exp(B_last)
     }
@@ -547,34 +556,48 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
   const int pA = lb0 + 32 * tr * RB, pB = lb0 + 32 * tc * RB;
   const int pA1 = lb1 + 32 * tr * RB, pB1 = lb1 + 32 * tc * RB;
 
-  // Slabs are multiplied from one LDS buffer while the next slab is copied into
-  // the other: one barrier per slab.  Prologue: the first chunk's factors and
-  // first slab in LDS.
+  // Prologue: the first chunk's factors in LDS, the first two slabs in flight.
   fetch_factors(chunk_of(0));
-  fetch_slab(0);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    fetch_slab(q, 0);
+    fetch_slab(q, 1);
+  }
   factors_part1(chunk_of(0));
   __syncthreads();
   factors_part2();
-  dma_wait();
   fetch_factors(chunk_of(min(1, N - 1)));
   __syncthreads();
 
+  // A wave's vector memory operations complete in order.  FL: the loads of
+  // fetch_factors, which lie between the copies of a chunk's first slab and
+  // those of its second.
+  constexpr int FL = NG ? RPT : 3 * RPT + (GB ? 4 : 0);
   for (int it = 0; it < N; ++it) {
     const int n = chunk_of(it), t0 = n * C;
     if (it > 0) store_totals(chunk_of(it - 1));
     const float gj = NG ? 1.f : sG[j];
-    const bool mine = dpw && (NG || n % a.KT == kt);  // this wave forms a tile of the chunk's dP
+    const bool shared = NG || (!REV && n % a.KT == kt);  // the workgroup forms the chunk's dP from all its tiles
+    const bool mine = dpw && shared;                     // this wave forms a tile of it
     f16v acc[2], accP;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = accP[e] = 0.f;
 #pragma unroll
     for (int sl = 0; sl < NSL; ++sl) {
       const int q = it * NSL + sl;
-      const bool b1 = (q & 1) != 0;  // this slab's buffer (even NSL: sl's parity)
-      T *sX = b1 ? sX1 : sX0, *sZ = b1 ? sZ1 : sZ0;
-      // the next slab into the other buffer, which the previous step's
-      // barrier freed
-      fetch_slab(q + 1);
+      constexpr int F0 = FL;
+      const bool last_slab = sl == NSL - 1;
+      const T *sX = (const T *)slot_of(w, q), *sZ = (const T *)(slot_of(w, q) + L::sub);
+      if (shared) {
+        // every wave's tiles have landed
+        if (sl == 0) dma_wait<2 * ND + F0>();
+        else dma_wait<2 * ND>();
+        __syncthreads();
+      } else if (sl == 0) {
+        dma_wait<3 * ND + F0>();
+      } else {
+        dma_wait<3 * ND>();
+      }
       if constexpr (GB && REV) {
         // dS_[n+1] for the value-side gate gradient, then D = dS_[n+1] gb, by
         // value row, before the chunk's products
@@ -590,32 +613,38 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         acc_split32<SPLIT, T>(S[sl], st, shi, slo);
 #pragma unroll
         for (int th = 0; th < NTT; ++th) {
-          const frag_t<T> xf = ld_slab_row<T>(sX, lb0, lb1, 32 * th, 32 * w + 16 * st);
+          const frag_t<T> xf = ld_slab_row<T>(sX, lb0, lb1, 32 * th, 16 * st);
           acc[th] = mma32<T>(acc[th], xf, shi);
           if constexpr (SPLIT) acc[th] = mma32<T>(acc[th], xf, slo);
         }
+      }
+      if (!shared) {
+        if (!last_slab) {
+          lds_wait();  // the row reads have returned
+          fetch_slab(q + 2, 0);
+        }
+        if (sl == 0) dma_wait<(NSL == 1 ? 2 : 3) * ND + F0>();
+        else if (last_slab) dma_wait<2 * ND>();
+        else dma_wait<3 * ND>();
       }
       // R^T <- gamma R^T + Z^T G
       if constexpr (!NG) S[sl] *= gj;
 #pragma unroll
       for (int u = 0; u < NST; ++u) {
-        const frag_t<T> zf = ld_slab_col_perm<T>(sZ, lt0, lt1, 16 * u, 32 * w);
+        const frag_t<T> zf = ld_slab_col_perm<T>(sZ, lt0, lt1, 16 * u, 0);
         S[sl] = mma32<T>(S[sl], zf, ld_row32<T>(sBh, L::LDTB, 0, 16 * u));
         if constexpr (SPLIT) S[sl] = mma32<T>(S[sl], zf, ld_row32<T>(sBl, L::LDTB, 0, 16 * u));
       }
-      if constexpr (NG) {
-        // (transposed, so that a lane holds consecutive columns of a row)
-        if (mine) {
-          const int steps = min(kVS, V - sl * kVS) / 16;
-#pragma unroll 4
-          for (int st = 0; st < steps; ++st)
-            accP = mma32<T>(accP, ld_slab_row<T>(sZ, pB, pB1, 0, 16 * st), ld_slab_row<T>(sX, pA, pA1, 0, 16 * st));
-        }
-      } else if constexpr (!REV) {
-        if (mine) {
-#pragma unroll
-          for (int st = 0; st < kVS / 16; ++st)
-            accP = mma32<T>(accP, ld_slab_row<T>(sX, pA, pA1, 0, 16 * st), ld_slab_row<T>(sZ, pB, pB1, 0, 16 * st));
+      if ((NG || !REV) && mine) {
+        // 16 columns at a time, from the wave that holds them (NG: transposed,
+        // so that a lane holds consecutive columns of a row)
+        const int steps = min(kVS, V - sl * kVS) / 16;
+#pragma unroll 2
+        for (int st = 0; st < steps; ++st) {
+          const char *tile = slot_of(st >> 1, q);
+          const frag_t<T> x = ld_slab_row<T>((const T *)tile, pA, pA1, 0, 16 * (st & 1));
+          const frag_t<T> z = ld_slab_row<T>((const T *)(tile + L::sub), pB, pB1, 0, 16 * (st & 1));
+          accP = NG ? mma32<T>(accP, z, x) : mma32<T>(accP, x, z);
         }
       }
       if constexpr (GB && !REV) {
@@ -626,9 +655,16 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         store_tile16<T>((T *)a.Sb + sb_index(bh, n, N, kt, a.KT, sl, NSL, w, kNW, l), S[sl]);
         __builtin_amdgcn_sched_barrier(0);
       }
-      // (publishes the next slab; every read of this slab's buffer is done)
-      dma_wait();
-      __syncthreads();
+      if (shared) {
+        __syncthreads();  // every read of the slab is done
+        if (!last_slab) {
+          fetch_slab(q + 2, 0);
+          fetch_slab(q + 2, 1);
+        }
+      } else if (!last_slab) {
+        lds_wait();  // the transpose reads have returned
+        fetch_slab(q + 2, 1);
+      }
     }
 
     // ---- dP of this key tile's chunks: masked, handed over transposed ([s][t])
@@ -649,21 +685,22 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
         }
       }
     }
-    // ---- the partials into the buffer of the chunk's last slab (the other
-    // one holds the next chunk's first slab): unit u (four rows) of feature j
-    // at unit u ^ (j mod CP/4); the next chunk's factor part 1 alongside
-    char *last = smem + (((it * NSL + NSL - 1) & 1) ? 2 * L::slab : 0);
-    float *sRed = (float *)last;
+    // ---- the partials into the wave's slot of the chunk's last slab (the
+    // other one holds the next chunk's first slab): unit u (four rows) of
+    // feature j at unit u ^ (j mod CP/4); the next chunk's factor part 1
+    // alongside
+    const int ql = it * NSL + NSL - 1;
     if constexpr (NG) {
       // ---- intra-chunk term: M = the chunk's masked X Z^T (rows x columns, hi
       // and lo for bf16; 16-byte chunk c of row r at c ^ (r mod 8)) through the
-      // buffer of the chunk's last slab, then acc += M G, wave w taking M's
+      // first waves' slots of the chunk's last slab, then acc += M G, wave w taking M's
       // columns 16 w .. +16 (the waves' partials are summed below anyway)
       constexpr int RM = CP * (int)sizeof(T), E = 16 / (int)sizeof(T);
       auto at = [&](int row, int col) {
         return row * RM + (((col / E) ^ (row & (RM / 16 - 1) & 7)) << 4) + (col % E) * (int)sizeof(T);
       };
-      char *sMh = last, *sMl = last + CP * RM;
+      static_assert((size_t)CP * RM <= L::slot, "M fits over a slot");
+      char *sMh = slot_of(0, ql), *sMl = slot_of(1, ql);
       if (dpw) {
         const int row = 32 * tr + j;
 #pragma unroll
@@ -707,7 +744,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         const int u = 8 * th + 2 * b + g;
-        *(f4 *)(sRed + (w * kKF + j) * CP + 4 * (u ^ (j & UM))) =
+        *(f4 *)((float *)slot_of(w, ql) + j * CP + 4 * (u ^ (j & UM))) =
             f4{acc[th][4 * b], acc[th][4 * b + 1], acc[th][4 * b + 2], acc[th][4 * b + 3]};
       }
     factors_part1(chunk_of(min(it + 1, N - 1)));
@@ -725,7 +762,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
 #pragma unroll
       for (int i4 = 0; i4 < RPT / 4; ++i4) {
         const int off = fk * CP + 4 * ((rg * (RPT / 4) + i4) ^ (fk & UM));
-        auto slot = [&](int p) { return *(const f4 *)(sRed + p * kKF * CP + off); };
+        auto slot = [&](int p) { return *(const f4 *)((const float *)slot_of(p, ql) + off); };
         const f4 s = (slot(0) + slot(1)) + (slot(2) + slot(3));
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -746,11 +783,14 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
     }
     // ---- the next chunk's factor part 2 (the last chunk redoes its own);
     // the barrier publishes its tiles and orders the combine's reads of the
-    // partials before the next slab store into their buffer
+    // partials before the copies into their slots
     factors_part2();
     fetch_factors(chunk_of(min(it + 2, N - 1)));
     __syncthreads();
+    fetch_slab(ql + 2, 0);
+    fetch_slab(ql + 2, 1);
   }
+  dma_wait();  // (no copy outlives the workgroup's LDS)
   store_totals(chunk_of(N - 1));
 
   // ---- final-state term of the gate gradient: rowsum(S_T (.) dS_T) per feature
