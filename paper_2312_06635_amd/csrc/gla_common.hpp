@@ -67,23 +67,31 @@ constexpr float kLog2e = 1.4426950408889634f;
 // log2 save the multiply by log2(e) that an exp() would add.
 __device__ __forceinline__ float exp2f_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// log alpha from the gate argument g: g itself when inv_tau == 0, else the
-// GLA gate epilogue alpha = sigmoid(g)^(1/tau) of Sec. 4.4, i.e. log alpha =
+// The GLA gate epilogue alpha = sigmoid(g)^(1/tau) of Sec. 4.4: log alpha =
 // logsigmoid(g) / tau with logsigmoid(g) = min(g, 0) - log1p(e), e =
 // exp(-|g|) in (0, 1]: log1p(e) is log(1 + e), or e (1 - e / 2) below 1e-3,
 // where 1 + e would lose e's low bits (absolute error < 1e-9 either way).
 // Elements outside the sequence (ok == false) contribute log alpha = 0.
-__device__ __forceinline__ float gate_la(float g, float inv_tau, bool ok) {
-  if (inv_tau == 0.f) return g;
-  const float e = __expf(-fabsf(g));
-  const float l1p = e < 1e-3f ? e * (1.f - 0.5f * e) : __logf(1.f + e);
-  return ok ? (fminf(g, 0.f) - l1p) * inv_tau : 0.f;
+// Both forms are evaluated and one is selected, with the hardware logarithm (1
+// + e needs no range handling): the library's logarithm put two branches around
+// each element, which the loops over a thread's rows ran one after the other
+// (forward + backward on 32 x 4 heads of 2048 steps, 128/256, bf16: 914 -> 873
+// us; errors against 64 bits unchanged, 1.7e-7 in fp32).
+__device__ __forceinline__ float gate_epilogue(float g, float inv_tau, bool ok) {
+  const float e = exp2f_fast(-kLog2e * fabsf(g));
+  const float small = e * (1.f - 0.5f * e), big = 0.693147180559945309f * __builtin_amdgcn_logf(1.f + e);
+  const float x = ((g < 0.f ? g : 0.f) - (e < 1e-3f ? small : big)) * inv_tau;
+  return ok ? x : 0.f;
 }
-// d log alpha / d g: 1, or sigmoid(-g) / tau for the gate epilogue.
+// log alpha from the gate argument g, which is log alpha itself when inv_tau == 0.
+__device__ __forceinline__ float gate_la(float g, float inv_tau, bool ok) {
+  return inv_tau == 0.f ? g : gate_epilogue(g, inv_tau, ok);
+}
+// d log alpha / d g of the gate epilogue: sigmoid(-g) / tau.
 // (the hardware reciprocal, within an ulp: a full division cost a tenth of the
-// in-chunk kernel with the epilogue)
+// in-chunk kernel)
 __device__ __forceinline__ float gate_dla_dg(float g, float inv_tau) {
-  return inv_tau == 0.f ? 1.f : inv_tau * __builtin_amdgcn_rcpf(1.f + __expf(g));
+  return inv_tau * __builtin_amdgcn_rcpf(1.f + exp2f_fast(kLog2e * g));
 }
 
 // ---------------------------------------------------------------- fragments
@@ -190,17 +198,6 @@ template <typename T, int ROWS, int COLS, int NT> struct TileLd {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       r[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? off[i] : 0x80000000u, 0, 0));
-  }
-  // store() into a tile whose 16-byte chunks are XOR-swizzled per row: chunk
-  // c of row r lands at chunk c ^ (((r & 3) << 2) | ((r >> 2) & 3)).
-  __device__ __forceinline__ void store_swz(T *dst, int ld) const {
-    const int row0 = (int)threadIdx.x / VPR, ch = (int)threadIdx.x % VPR;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int row = row0 + i * RSTEP;
-      const int cs = ch ^ (((row & 3) << 2) | ((row >> 2) & 3));
-      if (ROWS % RSTEP == 0 || row < ROWS) *(u32x4 *)(dst + row * ld + cs * EV) = r[i];
-    }
   }
   // store() into a 2-byte tile whose 8-byte units are XOR-permuted per row:
   // unit u of row r lands at unit u ^ sw(r) (sw(r) below the row's unit count).

@@ -37,7 +37,8 @@
 //        k (.) dk summed backwards over the chunk.
 // The traffic is q, k, the gate, dq_inter and dk_inter (fp32) and dP in, dq, dk
 // and the gate gradient out: 369 MB on 8 x 4 heads of 2048 steps at d_k = 256
-// in bf16, 75 us at the copy rate; measured 97-103 us.
+// in bf16, 75 us at the copy rate; measured 89 us (97-103 us with one exponential per
+// pair).
 #include <type_traits>
 
 #include "gla_common.hpp"
@@ -235,7 +236,7 @@ __global__ void __launch_bounds__(64 * (C / 16)) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float x = el_f<T>(rl[r]);
-      if constexpr (PRE) x = gate_la(x, a.inv_tau, fv && 16 * w + r < rv);
+      if constexpr (PRE) x = gate_epilogue(x, a.inv_tau, fv && 16 * w + r < rv);
       tot += x;
       al[r] = __expf(x);
       q[r] = el_f<T>(rq[r]);
@@ -464,7 +465,7 @@ intra_plain_kernel(IntraArgs a) {
     const auto rs_la = make_rsrc(a.la ? (const T *)a.la + (int64_t)bh * T_ + t0 : qc,
                                  a.la ? rsrc_bytes((int64_t)(T_ - t0) * esz) : 0u);
     float x = z = el_f<T>(ld_el<T>(rs_la, l < C ? (uint32_t)(l * esz) : 0x80000000u));
-    if constexpr (PRE) x = gate_la(x, a.inv_tau, l < rv);
+    if constexpr (PRE) x = gate_epilogue(x, a.inv_tau, l < rv);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const float y = __shfl_up(x, o);

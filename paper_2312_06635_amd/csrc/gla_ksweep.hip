@@ -44,7 +44,7 @@
 // 32 columns (LDS DMA, counted waits) into its own two slots and meets the
 // others once per chunk only, or per slab where a chunk's dP is formed.
 // Forward + backward against slabs shared by the workgroup, with a barrier
-// each: 128 heads x 2048 at 128/256 with the gate epilogue 938 -> 922 us, 512 x
+// each: 128 heads x 2048 at 128/256 with the gate epilogue 938 -> 922 us, 256 x
 // 2048 at 128/128 1286 -> 1253 us, 512 x 2048 at 64/64 without a gate 658 ->
 // 654 us, 32 x 2048 at 256/512 532 us either way.
 //
@@ -474,7 +474,7 @@ __device__ __forceinline__ void key_sweep(const KsArgs &a, char *smem, int wg) {
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
         float x = elem_f<T>(fla[i]);
-        if constexpr (PRE) x = gate_la(x, a.inv_tau, fthr && RPT * rg + i < rv);  // gate epilogue
+        if constexpr (PRE) x = gate_epilogue(x, a.inv_tau, fthr && RPT * rg + i < rv);  // gate epilogue
         s += x;
         al[i] = __expf(x);
       }

@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) p
 #pragma unroll
       for (int f = 0; f < FPL; ++f) {
         if constexpr (PRE) {
-          lav[r][f] = gate_la(x[f], a.inv_tau, fv && 16 * w + r < rv);
+          lav[r][f] = gate_epilogue(x[f], a.inv_tau, fv && 16 * w + r < rv);
           tot[f] += lav[r][f];
         } else {
           tot[f] += x[f];
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) p
     if constexpr (sizeof(T) == 2) raw = __builtin_amdgcn_raw_buffer_load_b16(rs_la, o1, 0, 0) << 16;
     else raw = __builtin_amdgcn_raw_buffer_load_b32(rs_la, o1, 0, 0);
     float x = __builtin_bit_cast(float, raw);
-    if constexpr (PRE) x = gate_la(x, a.inv_tau, l < rv);
+    if constexpr (PRE) x = gate_epilogue(x, a.inv_tau, l < rv);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const float y = __shfl_up(x, o);
