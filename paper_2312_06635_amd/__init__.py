@@ -123,6 +123,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _aligned(*tensors):
+    """The tensors, those that do not start on a 16-byte boundary copied: the
+    chunkwise kernels copy 16-byte chunks straight into LDS."""
+    if not any(t is not None and t.data_ptr() & 15 for t in tensors):
+        return tensors
+    return tuple(t.clone() if t is not None and t.data_ptr() & 15 else t for t in tensors)
+
+
 def _check(q, k, v, la, extra=(), states=()):
     if q.dim() != 4:
         raise ValueError("q must be [B, H, T, d_k]")
@@ -211,10 +219,11 @@ def chunk_fwd(q, k, v, log_alpha, chunk=64, subchunk=16, S0=None, output_final_s
     general form G_t = alpha_t^T beta_t (App. C; forward only).  segments
     fixes the sequence segments per head (GLA_SEGMENTS in include/gla.h: 1 =
     states on chip, T/chunk = every chunk's state materialized; 0 = decided
-    from the shape).  fp32_diagonal evaluates every diagonal sub-chunk block
-    in fp32 log space (GLA_FLAG_FP32_DIAGONAL) instead of on the matrix cores."""
+    from the shape).  fp32_diagonal (GLA_FLAG_FP32_DIAGONAL) changes nothing:
+    every diagonal sub-chunk block is evaluated in fp32 anyway."""
     _check(q, k, v, log_alpha, states=(("S0", S0),))
     _check_beta(log_beta, v)
+    q, k, v, log_alpha, S0, log_beta = _aligned(q, k, v, log_alpha, S0, log_beta)
     B, H, T, dk = q.shape
     dv = v.shape[3]
     flags = (stage << STAGE_SHIFT) | _segments_flag(segments) | (FLAG_FP32_DIAGONAL if fp32_diagonal else 0)
@@ -251,6 +260,7 @@ def chunk_fwd_noalloc(q, k, v, log_alpha, chunk=64, subchunk=16, S0=None, out=No
     _check(q, k, o, None, states=(("S_T", ST),))
     if o.shape != v.shape:
         raise ValueError("o must be shaped like v")
+    q, k, v, log_alpha, S0 = _aligned(q, k, v, log_alpha, S0)
     p = _problem(q, v, chunk, subchunk, 0, gate_tau, log_alpha)
     st = lib().gla_chunk_fwd_noalloc(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(S0),
                                      _ptr(o), _ptr(ST), _stream(q.device))
@@ -278,6 +288,7 @@ def chunk_bwd(q, k, v, log_alpha, dO, chunk=64, subchunk=16, S0=None, dST=None,
     _check(q, k, v, log_alpha, extra=(("dO", dO, v.shape[3]),), states=(("S0", S0), ("dST", dST)))
     _check_beta(log_beta, v)
     _check_beta(o, v)
+    q, k, v, log_alpha, dO, S0, dST, log_beta, o = _aligned(q, k, v, log_alpha, dO, S0, dST, log_beta, o)
     B, H, T, dk = q.shape
     dv = v.shape[3]
     flags = (FLAG_REUSE_FWD_WORKSPACE if reuse_fwd_workspace else 0) | (stage << STAGE_SHIFT) | \

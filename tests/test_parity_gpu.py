@@ -1138,3 +1138,36 @@ def test_ragged_sequence_segments(cfg):
     g1 = g.chunk_bwd(*args, d["dO"], cfg["chunk"], cfg["subchunk"], S0=d["S0"], dST=d["dST"], want_dS0=True, segments=1)
     torch.cuda.synchronize()
     compare(inp, o1, ST1, g1, idx, cfg["io"], cfg["name"] + ", one segment")
+
+
+@pytest.mark.parametrize("gate", [True, False])
+def test_inputs_off_a_16_byte_boundary(gate):
+    """Contiguous views that start 2 or 4 bytes into a buffer (a slice of a flat
+    parameter) give the bits of aligned tensors, segmented and not."""
+    g = gla()
+    for T in (192, 1000):
+        cfg = small_case("unaligned", "bf16", 1, 1, T, 64, 64, 16, 16, 71, s0_std=0.1)
+        inp = W.make_inputs(cfg, dST_std=0.1)
+        if not gate:
+            inp["log_alpha"] = None
+        d = to_dev(inp)
+
+        def off(t):
+            if t is None:
+                return None
+            flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+            flat[1:].copy_(t.flatten())
+            return flat[1:].view(t.shape)
+
+        def call(x):
+            o, ST = g.chunk_fwd(x["q"], x["k"], x["v"], x["log_alpha"], 16, 16, S0=x["S0"], output_final_state=True)
+            r = g.chunk_bwd(x["q"], x["k"], x["v"], x["log_alpha"], x["dO"], 16, 16, S0=x["S0"], dST=x["dST"],
+                            want_dS0=True)
+            return dict(r, o=o, ST=ST)
+
+        x = {n: off(t) for n, t in d.items()}
+        assert all(t is None or t.data_ptr() % 16 for t in x.values())
+        want, got = call(d), call(x)
+        torch.cuda.synchronize()
+        for n in want:
+            assert (want[n] is None and got[n] is None) or torch.equal(want[n], got[n]), n
