@@ -1171,3 +1171,17 @@ def test_inputs_off_a_16_byte_boundary(gate):
         torch.cuda.synchronize()
         for n in want:
             assert (want[n] is None and got[n] is None) or torch.equal(want[n], got[n]), n
+
+
+@pytest.mark.parametrize("io,V,C,K", [("bf16", 272, 64, 48), ("bf16", 384, 32, 64), ("bf16", 528, 64, 32), ("bf16", 768, 16, 64),
+                                      ("f32", 384, 64, 32), ("f32", 272, 16, 64), ("f32", 656, 32, 48)])
+def test_key_sweeps_over_three_and_six_slabs(io, V, C, K):
+    """d_v of three and of five or six slabs of 128 columns, the last one full or
+    nearly empty, a ragged last chunk: gated, ungated and general form."""
+    B, H, T = 1, 2, 3 * C + 7
+    cfg = small_case(f"slabs_{io}_{V}_{C}", io, B, H, T, K, V, C, 16, 81, s0_std=0.1)
+    inp = W.make_inputs(cfg, dST_std=0.1)
+    o, ST, gr = run_gpu(inp, C, 16, want_state=True)
+    compare(inp, o, ST, gr, list(range(B * H)), io, cfg["name"])
+    test_ungated_kernels(io, B, H, T, K, V, C, 16, 0)
+    test_general_gate_backward(io, B, H, T, K, V, C, 16, "mild")
